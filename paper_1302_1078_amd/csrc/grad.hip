@@ -5,12 +5,14 @@
 //                   x[colind[p]] that the forward stored (the save variant of
 //                   the SpMV): the same products, read as a stream
 // Rows are visited through the same bin table as the products (row groups of
-// G lanes, or one workgroup per segment of a split row); no cross-lane
-// reduction is needed because every nonzero is independent.
+// G lanes, or one workgroup per segment of a split row).  With k = 1 every
+// lane serves a nonzero of its own and no cross-lane reduction is needed;
+// with k > 1 the KL lanes of a slot share one nonzero (k_grad_wide).
 #include <mutex>
 
 #include "device.hpp"
 #include "internal.hpp"
+#include "product_impl.hpp"
 
 namespace spx {
 
@@ -63,11 +65,11 @@ __device__ __forceinline__ void merge_add(const MergeTab<XT>& tb, XT* y, int64_t
   atomicAdd(y + static_cast<int64_t>(c) * ldy, v);
 }
 
-template <typename VT, typename XT, int MODE, bool MERGE = false>
+template <typename VT, typename XT, int MODE>
 __device__ __forceinline__ void visit_run(const ProdArgs& a, int32_t row, int32_t p, int32_t p1, int step,
-                                          const MergeTab<XT>& tb = MergeTab<XT>{nullptr, nullptr}) {
-  const XT* dy = static_cast<const XT*>(a.X) + static_cast<int64_t>(row) * a.ldx;
-  const XT dy0 = (p < p1) ? dy[0] : XT(0);  // k = 1: one dY entry per row
+                                          const MergeTab<XT>& tb) {
+  // one dY entry per row
+  const XT dy0 = (p < p1) ? static_cast<const XT*>(a.X)[static_cast<int64_t>(row) * a.ldx] : XT(0);
   for (; p < p1; p += kVisit * step) {
     bool h[kVisit];
     int32_t c[kVisit];
@@ -84,36 +86,21 @@ __device__ __forceinline__ void visit_run(const ProdArgs& a, int32_t row, int32_
 #pragma unroll
       for (int u = 0; u < kVisit; ++u) {
         if (!h[u]) continue;
-        XT* dst = static_cast<XT*>(a.Y) + static_cast<int64_t>(c[u]) * a.ldy;
-        if constexpr (MERGE) merge_add(tb, static_cast<XT*>(a.Y), a.ldy, c[u], v[u] * dy0);
-        else if (a.k == 1) atomicAdd(dst, v[u] * dy0);
-        else
-          for (int t = 0; t < a.k; ++t) atomicAdd(dst + t, v[u] * dy[t]);
+        merge_add(tb, static_cast<XT*>(a.Y), a.ldy, c[u], v[u] * dy0);
       }
     } else {
       const XT* X2 = static_cast<const XT*>(a.X2);
-      if (MODE == kSddmmSaved || a.k == 1) {
-        XT xr[kVisit];
+      XT xr[kVisit];
 #pragma unroll
-        for (int u = 0; u < kVisit; ++u) {
-          if constexpr (MODE == kSddmmSaved) xr[u] = h[u] ? ld_stream(X2 + p + u * step) : XT(0);
-          else xr[u] = h[u] ? X2[static_cast<int64_t>(c[u]) * a.ldx2] : XT(0);
-        }
+      for (int u = 0; u < kVisit; ++u) {
+        if constexpr (MODE == kSddmmSaved) xr[u] = h[u] ? ld_stream(X2 + p + u * step) : XT(0);
+        else xr[u] = h[u] ? X2[static_cast<int64_t>(c[u]) * a.ldx2] : XT(0);
+      }
 #pragma unroll
-        for (int u = 0; u < kVisit; ++u) {
-          XT s = XT(0);
-          s = s + dy0 * xr[u];
-          if (h[u]) __builtin_nontemporal_store(s, static_cast<XT*>(a.Y) + p + u * step);
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < kVisit; ++u) {
-          if (!h[u]) continue;
-          const XT* xr = X2 + static_cast<int64_t>(c[u]) * a.ldx2;
-          XT s = XT(0);
-          for (int t = 0; t < a.k; ++t) s = s + dy[t] * xr[t];
-          __builtin_nontemporal_store(s, static_cast<XT*>(a.Y) + p + u * step);
-        }
+      for (int u = 0; u < kVisit; ++u) {
+        XT s = XT(0);
+        s = s + dy0 * xr[u];
+        if (h[u]) __builtin_nontemporal_store(s, static_cast<XT*>(a.Y) + p + u * step);
       }
     }
   }
@@ -124,9 +111,9 @@ __device__ __forceinline__ void visit_run(const ProdArgs& a, int32_t row, int32_
 // consecutive nonzeros (coalesced index loads and output stores), the row of
 // each comes from a lockstep search over the rows' offsets in LDS, and the
 // rows' dY entries are staged in LDS once.
-template <typename VT, typename XT, int MODE, bool MERGE = false>
+template <typename VT, typename XT, int MODE>
 __device__ __forceinline__ void visit_stream(const ProdArgs& a, const BinDesc& d, int tile,
-                                             const MergeTab<XT>& tb = MergeTab<XT>{nullptr, nullptr}) {
+                                             const MergeTab<XT>& tb) {
   constexpr int kStreamRows = kWG;  // a stream tile: one bin row per thread (the bin table's layout)
   constexpr int kChunk = 1024, kPer = kChunk / kWG;
   __shared__ int32_t s_off[kStreamRows + 1];
@@ -199,10 +186,7 @@ __device__ __forceinline__ void visit_stream(const ProdArgs& a, const BinDesc& d
         v[u] = static_cast<XT>(ValueLoad<VT>::get(static_cast<const VT*>(a.values) + p[u]));
 #pragma unroll
       for (int u = 0; u < kPer; ++u)
-        if (ok[u]) {
-          if constexpr (MERGE) merge_add(tb, static_cast<XT*>(a.Y), a.ldy, c[u], v[u] * s_dy[lo[u]]);
-          else atomicAdd(static_cast<XT*>(a.Y) + static_cast<int64_t>(c[u]) * a.ldy, v[u] * s_dy[lo[u]]);
-        }
+        if (ok[u]) merge_add(tb, static_cast<XT*>(a.Y), a.ldy, c[u], v[u] * s_dy[lo[u]]);
     } else {
       XT xr[kPer];
 #pragma unroll
@@ -220,10 +204,10 @@ __device__ __forceinline__ void visit_stream(const ProdArgs& a, const BinDesc& d
   }
 }
 
-// One workgroup's share of a backward traversal: the bin and tile of this
-// workgroup, then its split segment, stream tile or row groups.  With MERGE
-// the scatter adds go through the workgroup's table `tb`.
-template <typename VT, typename XT, int MODE, bool MERGE>
+// One workgroup's share of a backward traversal with k = 1: the bin and tile
+// of this workgroup, then its split segment, stream tile or row groups.  The
+// scatter adds go through the workgroup's table `tb`.
+template <typename VT, typename XT, int MODE>
 __device__ __forceinline__ void grad_tile(const ProdArgs& a, const MergeTab<XT>& tb) {
   const int b = blockIdx.x;
   int bi = 0;
@@ -240,23 +224,20 @@ __device__ __forceinline__ void grad_tile(const ProdArgs& a, const MergeTab<XT>&
     const int32_t re = a.rowptr[row + 1];
     const int32_t p0 = a.rowptr[row] + (tile - f) * a.chunk;
     const int32_t p1 = min(p0 + a.chunk, re);
-    visit_run<VT, XT, MODE, MERGE>(a, row, p0 + t, p1, kWG, tb);
+    visit_run<VT, XT, MODE>(a, row, p0 + t, p1, kWG, tb);
     return;
   }
-  if (d.lanes == SPX_LANES_STREAM && a.k == 1) {
-    visit_stream<VT, XT, MODE, MERGE>(a, d, tile, tb);
+  if (d.lanes == SPX_LANES_STREAM) {
+    visit_stream<VT, XT, MODE>(a, d, tile, tb);
     return;
   }
   // row groups of G lanes; a bin may give each group several rows (rpg),
-  // taken in the same order as the product kernels.  A stream bin's 256 rows
-  // per workgroup are served by 32 groups of 8 lanes, 8 rows each, so that
-  // the per-nonzero loads and stores of a row are contiguous across lanes.
-  const bool stream = (d.lanes == SPX_LANES_STREAM);
-  const int G = stream ? 8 : d.lanes;
-  const int rpg = stream ? 8 : d.rpg;  // 32 groups x 8 rows = the bin's 256 rows per workgroup
+  // taken in the same order as the product kernels
+  const int G = d.lanes;
+  const int rpg = d.rpg;
   const int ng = kWG / G;
   // every row id and range of the group first (independent loads), then the rows
-  constexpr int kMaxRpg = 8;
+  constexpr int kMaxRpg = 4;  // bins_from_plan gives 1 or 4
   int32_t rows[kMaxRpg], q0[kMaxRpg], q1[kMaxRpg];
 #pragma unroll
   for (int j = 0; j < kMaxRpg; ++j) {
@@ -273,16 +254,16 @@ __device__ __forceinline__ void grad_tile(const ProdArgs& a, const MergeTab<XT>&
   }
 #pragma unroll
   for (int j = 0; j < kMaxRpg; ++j)
-    if (rows[j] >= 0) visit_run<VT, XT, MODE, MERGE>(a, rows[j], q0[j] + t % G, q1[j], G, tb);
+    if (rows[j] >= 0) visit_run<VT, XT, MODE>(a, rows[j], q0[j] + t % G, q1[j], G, tb);
 }
 
 template <typename VT, typename XT, int MODE>
 __global__ __launch_bounds__(kWG) void k_grad(const ProdArgs a) {
-  grad_tile<VT, XT, MODE, false>(a, MergeTab<XT>{nullptr, nullptr});
+  grad_tile<VT, XT, MODE>(a, MergeTab<XT>{nullptr, nullptr});
 }
 
-// A^T dy with k = 1 through the workgroup's merge table: the same traversal as
-// k_grad<kScatterT>, then one atomic per distinct column of the workgroup.
+// A^T dy with k = 1 through the workgroup's merge table: the traversal of
+// k_grad, then one atomic per distinct column of the workgroup.
 template <typename VT, typename XT>
 __global__ __launch_bounds__(kWG) void k_scatter_merged(const ProdArgs a) {
   __shared__ int32_t s_key[kMergeSlots];
@@ -295,12 +276,134 @@ __global__ __launch_bounds__(kWG) void k_scatter_merged(const ProdArgs a) {
   __syncthreads();
   // the traversal's only barriers (a stream tile's) are reached by the whole
   // workgroup, and every thread then returns here to the barrier below
-  grad_tile<VT, XT, kScatterT, true>(a, MergeTab<XT>{s_key, s_val});
+  grad_tile<VT, XT, kScatterT>(a, MergeTab<XT>{s_key, s_val});
   __syncthreads();
   XT* y = static_cast<XT*>(a.Y);
   for (int i = t; i < kMergeSlots; i += kWG) {
     const int32_t c = s_key[i];
     if (c >= 0) atomicAdd(y + static_cast<int64_t>(c) * a.ldy, s_val[i]);
+  }
+}
+
+// k > 1: a row group of G lanes holds S = max(G, KL) / KL slots, and the KL
+// lanes of a slot take one nonzero at a time, VEC consecutive columns each
+// (the lane layout of the SpMM): the row of X is one contiguous access of the
+// slot instead of k separate ones of a single lane, each in a line of its own
+// beside 63 others.  What bounds it is the X row gather, as in the forward
+// SpMM.  Every round of kVisit nonzeros issues its index loads (each lane one,
+// shared by shuffle), then its gathers, then adds up.  k above KL x VEC runs
+// in column slabs inside the round, so out is written once.  Measured on a
+// power law of 262,144 rows and 5.2 M nonzeros, k = 16, FP32: forward, sampled
+// dot and transpose together 552 us with one lane per nonzero (the sampled
+// dot 410 of them), 202 us with four.
+template <typename VT, typename XT, int MODE, int KL, int VEC>
+__global__ __launch_bounds__(kWG) void k_grad_wide(const ProdArgs a) {
+  constexpr int U = kVisit;
+  constexpr int PER = (U + KL - 1) / KL;
+  int bi = 0;
+  while (bi + 1 < a.nbins && static_cast<int>(blockIdx.x) >= a.bins[bi + 1].blk_begin) ++bi;
+  const BinDesc d = a.bins[bi];
+  const int lb = blockIdx.x - d.blk_begin;
+  const int tile = (a.flags & SPX_FLAG_NO_XCD_MAP) ? lb : xcd_tile(lb, d.nblk);
+  const int t = threadIdx.x, kl = t % KL, base = t % kWave - kl;
+  // slots of the group, and this slot's first nonzero; the group's threads
+  // agree on all of these
+  int S;
+  int32_t row, p, p1;
+  if (d.lanes == 0) {  // one segment of a split row
+    if (tile >= d.nrows) return;
+    const int32_t s = a.seg_row[tile];
+    row = a.split_rows[s];
+    p = a.rowptr[row] + (tile - a.seg_first[s]) * a.chunk;
+    p1 = min(p + a.chunk, a.rowptr[row + 1]);
+    S = kWG / KL;
+    p += t / KL;
+  } else {
+    const int GG = max(d.lanes, KL);
+    const int idx = tile * (kWG / GG) + t / GG;
+    if (idx >= d.nrows) return;
+    prod::row_range(a, d, idx, row, p, p1);
+    S = GG / KL;
+    p += (t % GG) / KL;
+  }
+  const XT* dY = static_cast<const XT*>(a.X) + static_cast<int64_t>(row) * a.ldx;
+  XT dy[VEC];  // the first slab's columns
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) dy[e] = XT(0);
+  if (p < p1 && kl * VEC < a.k) prod::load_x<XT, VEC>(dY + kl * VEC, dy);
+  for (; p < p1; p += U * S) {
+    int32_t cl[PER], c[U];
+    bool h[U];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int u = kl + j * KL;
+      cl[j] = (u < U && p + u * S < p1) ? a.colind[p + u * S] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      h[u] = p + u * S < p1;
+      c[u] = __shfl(cl[u / KL], base + u % KL, kWave);
+    }
+    if constexpr (MODE == kScatterT) {
+      XT vl[PER], v[U];
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        const int u = kl + j * KL;
+        vl[j] = (u < U && p + u * S < p1) ? static_cast<XT>(ValueLoad<VT>::template get<false>(
+                                                static_cast<const VT*>(a.values) + p + u * S))
+                                          : XT(0);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = __shfl(vl[u / KL], base + u % KL, kWave);
+      for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
+        const int col = c0 + kl * VEC;
+        if (col >= a.k) continue;
+        if (c0 > 0) prod::load_x<XT, VEC>(dY + col, dy);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (!h[u]) continue;
+          XT* dst = static_cast<XT*>(a.Y) + static_cast<int64_t>(c[u]) * a.ldy + col;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) atomicAdd(dst + e, v[u] * dy[e]);
+        }
+      }
+      if (a.k > KL * VEC) prod::load_x<XT, VEC>(dY + kl * VEC, dy);
+    } else {
+      XT s[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) s[u] = XT(0);
+      for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
+        const int col = c0 + kl * VEC;
+        if (col >= a.k) continue;
+        if (c0 > 0) prod::load_x<XT, VEC>(dY + col, dy);
+        XT xv[U][VEC];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (h[u]) {
+            prod::load_x<XT, VEC>(static_cast<const XT*>(a.X2) + static_cast<int64_t>(c[u]) * a.ldx2 + col, xv[u]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) xv[u][e] = XT(0);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) s[u] = fma_t(dy[e], xv[u][e], s[u]);
+      }
+      if (a.k > KL * VEC) prod::load_x<XT, VEC>(dY + kl * VEC, dy);
+      // the slot's lanes are active together, so each exchange reads live lanes
+#pragma unroll
+      for (int u = 0; u < U; ++u) s[u] = group_sum<KL, 1>(s[u]);
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {  // lane kl stores the results kl, kl + KL, ... of its slot
+        XT out = s[(j * KL) % U];
+#pragma unroll
+        for (int u = j * KL + 1; u < U && u < (j + 1) * KL; ++u) out = (kl == u - j * KL) ? s[u] : out;
+        const int u = kl + j * KL;
+        if (u < U && p + u * S < p1) __builtin_nontemporal_store(out, static_cast<XT*>(a.Y) + p + u * S);
+      }
+    }
   }
 }
 
@@ -314,17 +417,36 @@ __global__ void k_zero_2d(XT* __restrict__ p, int64_t rows, int32_t k, int64_t l
 
 }  // namespace
 
-// Bin table for the per-nonzero traversals (bins_from_plan with KL = 1; the
-// traversal serves stream bins with 8-lane row groups whatever their size).
-static void grad_bins(const spx_plan* p, int32_t m, int32_t nnz, ProdArgs& a) {
-  if (p) {
-    bins_from_plan(p, a, 1, false);
-  } else {
-    const int32_t k = a.k;
-    a.k = 1;
-    bins_unbinned(m, nnz, 1, a);
-    a.k = k;
+// Bin table of a backward traversal with KL lanes per nonzero.
+static void grad_bins(const spx_plan* p, int32_t m, int32_t nnz, int kl, ProdArgs& a) {
+  if (p) bins_from_plan(p, a, kl, false);
+  else bins_unbinned(m, nnz, kl, a);
+}
+
+static unsigned grid_of(const ProdArgs& a) {
+  int64_t grid = 0;
+  for (int i = 0; i < a.nbins; ++i) grid = a.bins[i].blk_begin + a.bins[i].nblk;
+  return static_cast<unsigned>(grid);
+}
+
+// k > 1.  The lane layout is the SpMM's, so 16-byte loads need k, both leading
+// dimensions and both operands aligned to them (layout_for_k); otherwise, and
+// for the scatter (an atomic adds one element), a lane takes one column.
+template <typename VT, typename XT, int MODE>
+static spx_status launch_wide(const ProdArgs& a, int kl, int vec, unsigned g, hipStream_t st) {
+  constexpr int V = (MODE == kScatterT) ? 1 : 16 / sizeof(XT);
+#define SPX_WIDE(KL_, VEC_)                                           \
+  if (kl == KL_ && vec == VEC_) {                                     \
+    k_grad_wide<VT, XT, MODE, KL_, VEC_><<<g, kWG, 0, st>>>(a);       \
+    SPX_LAUNCHED("k_grad_wide");                                      \
+    return SPX_OK;                                                    \
   }
+  SPX_WIDE(2, 1) SPX_WIDE(4, 1) SPX_WIDE(8, 1) SPX_WIDE(16, 1) SPX_WIDE(32, 1)
+  if constexpr (V > 1) {
+    SPX_WIDE(1, V) SPX_WIDE(2, V) SPX_WIDE(4, V) SPX_WIDE(8, V) SPX_WIDE(16, V) SPX_WIDE(32, V)
+  }
+#undef SPX_WIDE
+  return fail(SPX_ERR_UNSUPPORTED, "no wide backward kernel for KL=%d VEC=%d", kl, vec);
 }
 
 spx_status launch_scatter_t(ProdArgs& a, const spx_plan* plan, int32_t m, int32_t n, int32_t nnz,
@@ -337,40 +459,44 @@ spx_status launch_scatter_t(ProdArgs& a, const spx_plan* plan, int32_t m, int32_
     else k_zero_2d<float><<<g, 256, 0, st>>>(static_cast<float*>(a.Y), n, a.k, a.ldy);
     SPX_LAUNCHED("k_zero_2d");
   }
-  grad_bins(plan, m, nnz, a);
-  int64_t grid = 0;
-  for (int i = 0; i < a.nbins; ++i) grid = a.bins[i].blk_begin + a.bins[i].nblk;
-  if (grid == 0) return SPX_OK;
-  const unsigned g = static_cast<unsigned>(grid);
-  if (a.k == 1) {  // contributions merged per workgroup first
-    if (vt == SPX_F64 && xt == SPX_F64) k_scatter_merged<double, double><<<g, kWG, 0, st>>>(a);
-    else if (vt == SPX_F32 && xt == SPX_F32) k_scatter_merged<float, float><<<g, kWG, 0, st>>>(a);
-    else if (vt == SPX_BF16 && xt == SPX_F32) k_scatter_merged<uint16_t, float><<<g, kWG, 0, st>>>(a);
-    else return fail(SPX_ERR_UNSUPPORTED, "csr_spmv_t: unsupported dtype pair");
-    SPX_LAUNCHED("k_scatter_merged");
-    return SPX_OK;
+  int kl = 1, vec = 1;
+  if (a.k > 1)
+    layout_for_k(a.k, static_cast<spx_dtype>(xt), a.X, a.ldx, a.Y, a.ldy, SPX_FLAG_SCALAR_X, &kl, &vec);
+  grad_bins(plan, m, nnz, kl, a);
+  const unsigned g = grid_of(a);
+  if (g == 0) return SPX_OK;
+  if (a.k > 1) {
+    if (vt == SPX_F64 && xt == SPX_F64) return launch_wide<double, double, kScatterT>(a, kl, vec, g, st);
+    if (vt == SPX_F32 && xt == SPX_F32) return launch_wide<float, float, kScatterT>(a, kl, vec, g, st);
+    if (vt == SPX_BF16 && xt == SPX_F32) return launch_wide<uint16_t, float, kScatterT>(a, kl, vec, g, st);
+    return fail(SPX_ERR_UNSUPPORTED, "csr_spmv_t: unsupported dtype pair");
   }
-  if (vt == SPX_F64 && xt == SPX_F64) k_grad<double, double, kScatterT><<<g, kWG, 0, st>>>(a);
-  else if (vt == SPX_F32 && xt == SPX_F32) k_grad<float, float, kScatterT><<<g, kWG, 0, st>>>(a);
-  else if (vt == SPX_BF16 && xt == SPX_F32) k_grad<uint16_t, float, kScatterT><<<g, kWG, 0, st>>>(a);
+  // k = 1: contributions merged per workgroup first
+  if (vt == SPX_F64 && xt == SPX_F64) k_scatter_merged<double, double><<<g, kWG, 0, st>>>(a);
+  else if (vt == SPX_F32 && xt == SPX_F32) k_scatter_merged<float, float><<<g, kWG, 0, st>>>(a);
+  else if (vt == SPX_BF16 && xt == SPX_F32) k_scatter_merged<uint16_t, float><<<g, kWG, 0, st>>>(a);
   else return fail(SPX_ERR_UNSUPPORTED, "csr_spmv_t: unsupported dtype pair");
-  SPX_LAUNCHED("k_grad<scatter>");
+  SPX_LAUNCHED("k_scatter_merged");
   return SPX_OK;
 }
 
 spx_status launch_sddmm(ProdArgs& a, const spx_plan* plan, int32_t m, int32_t nnz, int dt, bool saved,
                         hipStream_t st) {
-  grad_bins(plan, m, nnz, a);
-  int64_t grid = 0;
-  for (int i = 0; i < a.nbins; ++i) grid = a.bins[i].blk_begin + a.bins[i].nblk;
-  if (grid == 0) return SPX_OK;
-  const unsigned g = static_cast<unsigned>(grid);
   if (saved && a.k != 1) return fail(SPX_ERR_INVALID, "csr_sddmm_saved: k must be 1");
+  if (dt != SPX_F64 && dt != SPX_F32) return fail(SPX_ERR_UNSUPPORTED, "csr_sddmm: dtype must be F64 or F32");
+  int kl = 1, vec = 1;
+  if (a.k > 1)
+    layout_for_k(a.k, static_cast<spx_dtype>(dt), a.X, a.ldx, a.X2, a.ldx2, plan ? plan->opts.flags : 0u, &kl, &vec);
+  grad_bins(plan, m, nnz, kl, a);
+  const unsigned g = grid_of(a);
+  if (g == 0) return SPX_OK;
+  if (a.k > 1)
+    return dt == SPX_F64 ? launch_wide<double, double, kSddmm>(a, kl, vec, g, st)
+                         : launch_wide<float, float, kSddmm>(a, kl, vec, g, st);
   if (dt == SPX_F64 && saved) k_grad<double, double, kSddmmSaved><<<g, kWG, 0, st>>>(a);
-  else if (dt == SPX_F32 && saved) k_grad<float, float, kSddmmSaved><<<g, kWG, 0, st>>>(a);
+  else if (saved) k_grad<float, float, kSddmmSaved><<<g, kWG, 0, st>>>(a);
   else if (dt == SPX_F64) k_grad<double, double, kSddmm><<<g, kWG, 0, st>>>(a);
-  else if (dt == SPX_F32) k_grad<float, float, kSddmm><<<g, kWG, 0, st>>>(a);
-  else return fail(SPX_ERR_UNSUPPORTED, "csr_sddmm: dtype must be F64 or F32");
+  else k_grad<float, float, kSddmm><<<g, kWG, 0, st>>>(a);
   SPX_LAUNCHED(saved ? "k_grad<sddmm_saved>" : "k_grad<sddmm>");
   return SPX_OK;
 }
