@@ -5,9 +5,13 @@
 // in colind[rowptr[i] .. rowptr[i+1]-1].  Canonical form here: columns
 // strictly ascending inside a row; duplicate (i, j) triplets summed in input
 // order.  A stable radix sort on the key (row, column) keeps duplicates in
-// input order, so each run is summed front to back with plain FP64 adds.
+// input order, so each run is summed front to back with plain FP64 adds.  The values travel
+// with the keys: fetching them by position after the sort costs a random
+// 8-byte read per triplet, more than the 4 bytes per triplet and pass that an
+// index would save.
 #include "device.hpp"
 #include "internal.hpp"
+#include "radix.hpp"
 
 namespace spx {
 
@@ -22,63 +26,117 @@ inline int bits_for(int64_t x) {  // bits needed to represent x >= 0
   return b;
 }
 
-__global__ void k_make_keys(const int32_t* __restrict__ r, const int32_t* __restrict__ c,
-                            int64_t nnz, int32_t m, int32_t n, int cbits,
-                            uint64_t* __restrict__ keys, int32_t* __restrict__ vals,
-                            int32_t* __restrict__ bad) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= nnz) return;
-  const int32_t ri = r[i], ci = c[i];
-  if (ri < 0 || ri >= m || ci < 0 || ci >= n) {
-    atomicOr(bad, 1);
-    keys[i] = 0;
-  } else {
-    keys[i] = (static_cast<uint64_t>(ri) << cbits) | static_cast<uint64_t>(ci);
+// Triplets as the source of the first sort pass.  A triplet out of range sets
+// *bad and sorts as (0, 0).
+struct CooSrc {
+  const int32_t* r;
+  const int32_t* c;
+  const double* v;
+  int32_t m, n;
+  int cbits;
+  int32_t* bad;
+  __device__ __forceinline__ int2 raw(int64_t i) const { return make_int2(r[i], c[i]); }
+  __device__ __forceinline__ bool ok(int2 x) const {
+    return static_cast<uint32_t>(x.x) < static_cast<uint32_t>(m) && static_cast<uint32_t>(x.y) < static_cast<uint32_t>(n);
   }
-  vals[i] = static_cast<int32_t>(i);
+  __device__ __forceinline__ uint64_t key(int2 x) const {
+    return ok(x) ? (static_cast<uint64_t>(x.x) << cbits) | static_cast<uint64_t>(x.y) : 0;
+  }
+  __device__ __forceinline__ void check(int2 x) const {
+    if (!ok(x)) atomicOr(bad, 1);
+  }
+  __device__ __forceinline__ double val(int64_t i) const { return v[i]; }
+};
+
+// Heads of a tile: sorted positions whose key differs from the one before.
+__device__ __forceinline__ bool is_head(const uint64_t* keys, int64_t i) { return i == 0 || keys[i] != keys[i - 1]; }
+
+__global__ __launch_bounds__(kWG) void k_count_heads(const uint64_t* __restrict__ keys, int64_t nnz,
+                                                     int32_t* __restrict__ counts) {
+  __shared__ int32_t wsum[radix::kWaves];
+  const int64_t base = static_cast<int64_t>(blockIdx.x) * radix::kTile;
+  int32_t c = 0, all;
+#pragma unroll
+  for (int j = 0; j < radix::kItems; ++j) {
+    const int64_t i = base + j * kWG + threadIdx.x;
+    if (i < nnz) c += is_head(keys, i);
+  }
+  (void)radix::block_excl_scan(c, wsum, &all);
+  if (threadIdx.x == 0) counts[blockIdx.x] = all;
 }
 
-__global__ void k_heads(const uint64_t* __restrict__ keys, int64_t nnz, int32_t* __restrict__ heads) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= nnz) return;
-  heads[i] = (i == 0 || keys[i] != keys[i - 1]) ? 1 : 0;
-}
-
-// One thread per sorted position; heads emit their run.  `pos` holds the
-// exclusive scan of the head flags (the output index of each head).
-__global__ void k_emit(const uint64_t* __restrict__ keys, const int32_t* __restrict__ src,
-                       const int32_t* __restrict__ pos, const double* __restrict__ v,
-                       int64_t nnz, int32_t m, int cbits, int32_t* __restrict__ rowptr,
-                       int32_t* __restrict__ colind, double* __restrict__ values) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= nnz) return;
-  const uint64_t key = keys[i];
-  if (i > 0 && keys[i - 1] == key) return;  // not a head
-  const int32_t out = pos[i];
-  double s = v[src[i]];
-  int64_t j = i + 1;
-  while (j < nnz && keys[j] == key) {
-    s = s + v[src[j]];
-    ++j;
+// Every head emits its run.  offs: the exclusive scan of the tiles' head
+// counts; a head's place inside the tile comes from ballots, in sorted order.
+__global__ __launch_bounds__(kWG) void k_emit(const uint64_t* __restrict__ keys, const double* __restrict__ v,
+                                              const int32_t* __restrict__ offs, const int32_t* __restrict__ bad,
+                                              const int32_t* __restrict__ total, int64_t nnz, int32_t m, int cbits,
+                                              int32_t* __restrict__ rowptr, int32_t* __restrict__ colind,
+                                              double* __restrict__ values, int32_t* __restrict__ nnz_out) {
+  __shared__ int32_t wcnt[radix::kWaves];
+  const int t = threadIdx.x, lane = t % kWave, w = t / kWave;
+  const uint64_t lt_mask = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+  const int64_t base = static_cast<int64_t>(blockIdx.x) * radix::kTile + w * (radix::kTile / radix::kWaves);
+  if (blockIdx.x == 0 && t == 0) *nnz_out = (*bad) ? -1 : *total;
+  // the wavefront's keys and values, all loads issued at once; the key before
+  // each comes from the lane before it
+  uint64_t key[radix::kItems], heads[radix::kItems];
+  double val[radix::kItems];
+#pragma unroll
+  for (int j = 0; j < radix::kItems; ++j) {
+    const int64_t i = base + j * kWave + lane;
+    key[j] = i < nnz ? keys[i] : ~0ull;
+    val[j] = i < nnz ? v[i] : 0.0;
   }
-  const uint64_t cmask = (cbits >= 64) ? ~0ull : ((1ull << cbits) - 1ull);
-  colind[out] = static_cast<int32_t>(key & cmask);
-  values[out] = s;
-  const int32_t row = static_cast<int32_t>(key >> cbits);
-  const int32_t prev = (i == 0) ? -1 : static_cast<int32_t>(keys[i - 1] >> cbits);
-  for (int32_t rr = prev + 1; rr <= row; ++rr) rowptr[rr] = out;
-  if (j == nnz)
-    for (int32_t rr = row + 1; rr <= m; ++rr) rowptr[rr] = out + 1;
+  uint64_t carry = (base > 0 && base < nnz) ? keys[base - 1] : ~0ull;
+  const uint64_t first = carry;
+  int32_t mine = 0;
+#pragma unroll
+  for (int j = 0; j < radix::kItems; ++j) {
+    const int64_t i = base + j * kWave + lane;
+    const uint64_t up = __shfl_up(key[j], 1, kWave);
+    const uint64_t prev = lane == 0 ? carry : up;
+    heads[j] = __ballot(i < nnz && (i == 0 || key[j] != prev));
+    carry = __shfl(key[j], kWave - 1, kWave);
+    mine += __popcll(heads[j]);
+  }
+  if (lane == 0) wcnt[w] = mine;
+  __syncthreads();
+  int32_t run = offs[blockIdx.x];
+  for (int i = 0; i < w; ++i) run += wcnt[i];
+  const uint64_t cmask = (1ull << cbits) - 1ull;
+  carry = first;
+#pragma unroll
+  for (int j = 0; j < radix::kItems; ++j) {
+    const int64_t i = base + j * kWave + lane;
+    const uint64_t up = __shfl_up(key[j], 1, kWave);
+    const uint64_t before = lane == 0 ? carry : up;
+    carry = __shfl(key[j], kWave - 1, kWave);
+    if ((heads[j] >> lane) & 1) {
+      const int32_t out = run + __popcll(heads[j] & lt_mask);
+      double s = val[j];
+      int64_t q = i + 1;
+      // a run of one, unless the next position of this wavefront's 64 is no head
+      const bool alone = lane + 1 < kWave && q < nnz && ((heads[j] >> (lane + 1)) & 1);
+      if (!alone)
+        while (q < nnz && keys[q] == key[j]) {
+          s = s + v[q];
+          ++q;
+        }
+      colind[out] = static_cast<int32_t>(key[j] & cmask);
+      values[out] = s;
+      const int32_t row = static_cast<int32_t>(key[j] >> cbits);
+      const int32_t prev = (i == 0) ? -1 : static_cast<int32_t>(before >> cbits);
+      for (int32_t rr = prev + 1; rr <= row; ++rr) rowptr[rr] = out;
+      if (q == nnz)
+        for (int32_t rr = row + 1; rr <= m; ++rr) rowptr[rr] = out + 1;
+    }
+    run += __popcll(heads[j]);
+  }
 }
 
 __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t value) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) p[i] = value;
-}
-
-__global__ void k_finish_count(const int32_t* __restrict__ bad, const int32_t* __restrict__ total,
-                               int32_t* __restrict__ nnz_out) {
-  *nnz_out = (*bad) ? -1 : *total;
 }
 
 __global__ void k_validate(int32_t m, int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
@@ -107,34 +165,57 @@ __global__ void k_validate(int32_t m, int32_t n, int32_t nnz, const int32_t* __r
   }
 }
 
-__global__ void k_col_keys(const int32_t* __restrict__ colind, int64_t nnz, uint32_t* __restrict__ keys,
-                           int32_t* __restrict__ vals) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= nnz) return;
-  keys[i] = static_cast<uint32_t>(colind[i]);
-  vals[i] = static_cast<int32_t>(i);
+// Row of each nonzero.
+__global__ __launch_bounds__(kWG) void k_expand_rows(const int32_t* __restrict__ rowptr, int32_t m, int32_t nnz,
+                                                     int32_t* __restrict__ rowid) {
+  __shared__ int32_t s_row[radix::kTile];
+  __shared__ int32_t s_wsum[radix::kWaves];
+  const int t = threadIdx.x, lane = t % kWave, w = t / kWave;
+  const int32_t base = static_cast<int32_t>(blockIdx.x) * radix::kTile;
+  const int32_t here = min(radix::kTile, nnz - base);
+  int32_t row[radix::kItems];
+  radix::tile_rows(rowptr, m, base, here, s_row, s_wsum, row);
+#pragma unroll
+  for (int j = 0; j < radix::kItems; ++j) {
+    const int32_t i = w * (radix::kTile / radix::kWaves) + j * kWave + lane;
+    if (i < here) rowid[base + i] = row[j];
+  }
 }
 
-// After the stable sort by column: rowind from the CSR position by binary
-// search in rowptr, colptr from the column boundaries.
-__global__ void k_csc_finish(const uint32_t* __restrict__ keys, const int32_t* __restrict__ perm,
-                             const int32_t* __restrict__ rowptr, int32_t m, int32_t n, int64_t nnz,
-                             int32_t* __restrict__ rowind, int32_t* __restrict__ colptr) {
+// CSR nonzeros as the source of a sort by column: the payload is the row and
+// the CSR position, so neither is looked up after the sort.
+struct ColSrc {
+  const int32_t* colind;
+  const int32_t* rowid;
+  __device__ __forceinline__ uint32_t raw(int64_t i) const { return static_cast<uint32_t>(colind[i]); }
+  __device__ __forceinline__ uint32_t key(uint32_t x) const { return x; }
+  __device__ __forceinline__ void check(uint32_t) const {}
+  __device__ __forceinline__ uint64_t val(int64_t i) const {
+    return (static_cast<uint64_t>(static_cast<uint32_t>(rowid[i])) << 32) | static_cast<uint64_t>(i);
+  }
+};
+
+struct CscSink {
+  uint32_t* keys;
+  int32_t* rowind;
+  int32_t* perm;
+  __device__ __forceinline__ void put_key(int64_t q, uint32_t k) const { keys[q] = k; }
+  __device__ __forceinline__ void put_val(int64_t q, uint64_t v) const {
+    rowind[q] = static_cast<int32_t>(v >> 32);
+    perm[q] = static_cast<int32_t>(v & 0xffffffffu);
+  }
+};
+
+// colptr from the column boundaries of the sorted columns.
+__global__ void k_colptr(const uint32_t* __restrict__ keys, int32_t n, int64_t nnz, int32_t* __restrict__ colptr) {
   const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (q >= nnz) return;
-  const int32_t p = perm[q];
-  int32_t lo = 0, hi = m;  // largest row with rowptr[row] <= p
-  while (hi - lo > 1) {
-    int32_t mid = (lo + hi) >> 1;
-    if (rowptr[mid] <= p) lo = mid; else hi = mid;
-  }
-  rowind[q] = lo;
   // column ids are assumed valid (0 <= col < n); clamp so a bad id cannot
   // write outside colptr
-  const int32_t col = min(static_cast<int32_t>(keys[q]), n - 1);
-  const int32_t prev = (q == 0) ? -1 : min(static_cast<int32_t>(keys[q - 1]), n - 1);
-  if (q == 0 || prev != col)
-    for (int32_t j = prev + 1; j <= col; ++j) colptr[j] = static_cast<int32_t>(q);
+  const int32_t last = n - 1;
+  const int32_t col = static_cast<int32_t>(min(keys[q], static_cast<uint32_t>(last)));
+  const int32_t prev = (q == 0) ? -1 : static_cast<int32_t>(min(keys[q - 1], static_cast<uint32_t>(last)));
+  for (int32_t j = prev + 1; j <= col; ++j) colptr[j] = static_cast<int32_t>(q);
   if (q == nnz - 1)
     for (int32_t j = col + 1; j <= n; ++j) colptr[j] = static_cast<int32_t>(nnz);
 }
@@ -144,9 +225,9 @@ inline unsigned grid_for(int64_t n, int bs = 256) {
 }
 
 struct CooWs {
-  uint64_t* keys;
-  int32_t* src;
-  int32_t* heads;
+  uint64_t* keys[2];
+  double* vals;
+  int32_t* counts;
   int32_t* bad;
   int32_t* total;
   void* radix;
@@ -155,14 +236,37 @@ struct CooWs {
 
 CooWs carve_coo(void* ws, int64_t nnz, size_t* bytes) {
   Carve cv(ws, ~size_t(0));
+  const int64_t e = nnz > 0 ? nnz : 1;
   CooWs w;
-  w.keys = cv.take<uint64_t>(nnz > 0 ? nnz : 1);
-  w.src = cv.take<int32_t>(nnz > 0 ? nnz : 1);
-  w.heads = cv.take<int32_t>(nnz > 0 ? nnz : 1);
+  w.keys[0] = cv.take<uint64_t>(e);
+  w.keys[1] = cv.take<uint64_t>(e);
+  w.vals = cv.take<double>(e);
+  w.counts = cv.take<int32_t>(radix::tiles_of(e));
   w.bad = cv.take<int32_t>(1);
   w.total = cv.take<int32_t>(1);
-  w.radix = cv.take<char>(radix_workspace_bytes(nnz, 8));
-  w.scan = cv.take<char>(scan_workspace_bytes(nnz));
+  w.radix = cv.take<char>(radix::count_bytes(e));
+  w.scan = cv.take<char>(scan_workspace_bytes(radix::tiles_of(e)));
+  *bytes = cv.used;
+  return w;
+}
+
+struct CscWs {
+  int32_t* rowid;
+  uint32_t* keys[2];
+  uint64_t* vals[2];
+  void* radix;
+};
+
+CscWs carve_csc(void* ws, int64_t nnz, size_t* bytes) {
+  Carve cv(ws, ~size_t(0));
+  const int64_t e = nnz > 0 ? nnz : 1;
+  CscWs w;
+  w.rowid = cv.take<int32_t>(e);
+  for (int i = 0; i < 2; ++i) {
+    w.keys[i] = cv.take<uint32_t>(e);
+    w.vals[i] = cv.take<uint64_t>(e);
+  }
+  w.radix = cv.take<char>(radix::count_bytes(e));
   *bytes = cv.used;
   return w;
 }
@@ -218,19 +322,22 @@ extern "C" spx_status csr_from_coo(int32_t m, int32_t n, int64_t nnz_in, const i
     SPX_LAUNCHED("k_fill_i32");
     return SPX_OK;
   }
-  k_make_keys<<<grid_for(nnz_in), 256, 0, st>>>(r, c, nnz_in, m, n, cbits, w.keys, w.src, w.bad);
-  SPX_LAUNCHED("k_make_keys");
-  spx_status s = radix_sort_u64(w.keys, w.src, nnz_in, cbits + rbits, w.radix, st);
+  // the last pass lands in the workspace (the output `values` serves as the
+  // other payload buffer: k_emit reads sorted pairs while it writes)
+  const int bits = cbits + rbits, fin = (radix::passes_for(bits) & 1) ? 0 : 1;
+  radix::Pairs<uint64_t, double> buf[2];
+  for (int i = 0; i < 2; ++i) buf[i] = {w.keys[i], i == fin ? w.vals : values};
+  const CooSrc src{r, c, v, m, n, cbits, w.bad};
+  spx_status s = radix::sort(src, buf[0], buf[1], buf[fin], nnz_in, bits, w.radix, st);
   if (s != SPX_OK) return s;
-  k_heads<<<grid_for(nnz_in), 256, 0, st>>>(w.keys, nnz_in, w.heads);
-  SPX_LAUNCHED("k_heads");
-  s = exclusive_scan_i32(w.heads, w.heads, nnz_in, w.total, w.scan, st);
+  const unsigned tiles = static_cast<unsigned>(radix::tiles_of(nnz_in));
+  k_count_heads<<<tiles, kWG, 0, st>>>(buf[fin].k, nnz_in, w.counts);
+  SPX_LAUNCHED("k_count_heads");
+  s = exclusive_scan_i32(w.counts, w.counts, tiles, w.total, w.scan, st);
   if (s != SPX_OK) return s;
-  k_emit<<<grid_for(nnz_in), 256, 0, st>>>(w.keys, w.src, w.heads, v, nnz_in, m, cbits, rowptr,
-                                           colind, values);
+  k_emit<<<tiles, kWG, 0, st>>>(buf[fin].k, buf[fin].v, w.counts, w.bad, w.total, nnz_in, m, cbits, rowptr, colind,
+                                values, nnz_out);
   SPX_LAUNCHED("k_emit");
-  k_finish_count<<<1, 1, 0, st>>>(w.bad, w.total, nnz_out);
-  SPX_LAUNCHED("k_finish_count");
   return SPX_OK;
 }
 
@@ -255,7 +362,9 @@ extern "C" spx_status csr_validate(int32_t m, int32_t n, int32_t nnz, const int3
 
 namespace {
 size_t transpose_ws(int64_t nnz) {
-  return align_up(static_cast<size_t>(nnz > 0 ? nnz : 1) * 4) + radix_workspace_bytes(nnz, 4);
+  size_t bytes;
+  carve_csc(nullptr, nnz, &bytes);
+  return bytes;
 }
 }  // namespace
 
@@ -287,14 +396,16 @@ extern "C" spx_status csr_transpose_index(int32_t m, int32_t n, int32_t nnz, con
     SPX_LAUNCHED("k_fill_i32");
     return SPX_OK;
   }
-  Carve cv(workspace, ws_bytes);
-  uint32_t* keys = cv.take<uint32_t>(nnz);
-  void* rws = cv.take<char>(radix_workspace_bytes(nnz, 4));
-  k_col_keys<<<grid_for(nnz), 256, 0, st>>>(colind, nnz, keys, perm);
-  SPX_LAUNCHED("k_col_keys");
-  spx_status s = radix_sort_u32(keys, perm, nnz, bits_for(n > 0 ? n - 1 : 0), rws, st);
+  size_t need;
+  const CscWs w = carve_csc(workspace, nnz, &need);
+  const unsigned tiles = static_cast<unsigned>(radix::tiles_of(nnz));
+  k_expand_rows<<<tiles, kWG, 0, st>>>(rowptr, m, nnz, w.rowid);
+  SPX_LAUNCHED("k_expand_rows");
+  const int bits = bits_for(n > 0 ? n - 1 : 0), fin = (radix::passes_for(bits) & 1) ? 0 : 1;
+  const radix::Pairs<uint32_t, uint64_t> a{w.keys[0], w.vals[0]}, b{w.keys[1], w.vals[1]};
+  spx_status s = radix::sort(ColSrc{colind, w.rowid}, a, b, CscSink{w.keys[fin], rowind, perm}, nnz, bits, w.radix, st);
   if (s != SPX_OK) return s;
-  k_csc_finish<<<grid_for(nnz), 256, 0, st>>>(keys, perm, rowptr, m, n, nnz, rowind, colptr);
-  SPX_LAUNCHED("k_csc_finish");
+  k_colptr<<<grid_for(nnz), 256, 0, st>>>(w.keys[fin], n, nnz, colptr);
+  SPX_LAUNCHED("k_colptr");
   return SPX_OK;
 }

@@ -20,6 +20,7 @@
 
 #include "device.hpp"
 #include "internal.hpp"
+#include "radix.hpp"
 
 namespace spx {
 namespace {
@@ -41,8 +42,10 @@ bool shape_ok(int a, int b) {
 }
 
 struct BlockWs {
-  uint64_t* keys;
-  int32_t* src;
+  uint64_t* keys;  // sorted by sort_blocks, which may exchange keys / src
+  int32_t* src;    // with keys2 / src2
+  uint64_t* keys2;
+  int32_t* src2;
   int32_t* rowid;
   int32_t* index;  // exclusive scan of the block heads: block of each sorted entry
   int32_t* brow;   // block row of each block
@@ -61,7 +64,9 @@ BlockWs carve_blocks(void* ws, int64_t nnz, size_t* bytes) {
   w.index = cv.take<int32_t>(e);
   w.brow = cv.take<int32_t>(e);
   w.total = cv.take<int32_t>(1);
-  w.radix = cv.take<char>(radix_workspace_bytes(nnz, 8));
+  w.keys2 = cv.take<uint64_t>(e);
+  w.src2 = cv.take<int32_t>(e);
+  w.radix = cv.take<char>(radix::count_bytes(e));
   w.scan = cv.take<char>(scan_workspace_bytes(nnz));
   *bytes = cv.used;
   return w;
@@ -145,14 +150,20 @@ __global__ void k_block_rowptr(const int32_t* __restrict__ brow, const int32_t* 
 }
 
 spx_status sort_blocks(int32_t m, int32_t n, int32_t nnz, const int32_t* rowptr, const int32_t* colind, int a,
-                       int b, const BlockWs& w, int* cbits_out, hipStream_t st) {
+                       int b, BlockWs& w, int* cbits_out, hipStream_t st) {
   const int64_t mb = (static_cast<int64_t>(m) + a - 1) / a, nbc = (static_cast<int64_t>(n) + b - 1) / b;
   const int cbits = bits_for(nbc > 0 ? nbc - 1 : 0), rbits = bits_for(mb > 0 ? mb - 1 : 0);
   *cbits_out = cbits;
   k_block_keys<<<blocks_for(m), 256, 0, st>>>(rowptr, colind, m, a, b, cbits, w.keys, w.src, w.rowid);
   SPX_LAUNCHED("k_block_keys");
-  spx_status s = radix_sort_u64(w.keys, w.src, nnz, cbits + rbits, w.radix, st);
+  const radix::Pairs<uint64_t, int32_t> in{w.keys, w.src}, other{w.keys2, w.src2};
+  const bool odd = radix::passes_for(cbits + rbits) & 1;
+  const spx_status s = radix::sort(in, other, in, odd ? other : in, nnz, cbits + rbits, w.radix, st);
   if (s != SPX_OK) return s;
+  if (odd) {
+    w.keys = other.k;
+    w.src = other.v;
+  }
   k_block_heads<<<blocks_for(nnz), 256, 0, st>>>(w.keys, nnz, w.index);
   SPX_LAUNCHED("k_block_heads");
   return exclusive_scan_i32(w.index, w.index, nnz, w.total, w.scan, st);

@@ -13,6 +13,7 @@
 #include "device.hpp"
 #include "internal.hpp"
 #include "product_impl.hpp"
+#include "radix.hpp"
 
 namespace spx {
 
@@ -517,29 +518,99 @@ spx_status launch_sddmm(ProdArgs& a, const spx_plan* plan, int32_t m, int32_t nn
 namespace spx {
 namespace {
 
-__global__ void k_inv_perm(const int32_t* __restrict__ perm, int32_t nnz, int32_t* __restrict__ pos) {
-  const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (q >= nnz) return;
-  const int32_t p = perm[q];
-  if (p >= 0 && p < nnz) pos[p] = static_cast<int32_t>(q);
-}
+// The map's block b: its CSC positions q = b x SPX_CSC_BLOCK + i in ascending
+// nonzero p = perm[q].  The block is sorted by p in LDS (LSD digits of 8 bits,
+// ranked per wavefront as radix::k_scatter does), which leaves one read of
+// perm, the scattered write of dest and the write of local; inverting perm and
+// sorting nonzeros by block moved every nonzero through memory ten times
+// (2.6 M nonzeros: 50 us here, about 140 us that way).
+constexpr int kMapThreads = 512;
+constexpr int kMapItems = SPX_CSC_BLOCK / kMapThreads;
+constexpr int kMapWaves = kMapThreads / kWave;
 
-__global__ void k_block_keys(const int32_t* __restrict__ pos, int32_t nnz, uint32_t* __restrict__ keys,
-                             int32_t* __restrict__ vals) {
-  const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p >= nnz) return;
-  keys[p] = static_cast<uint32_t>(pos[p]) / SPX_CSC_BLOCK;
-  vals[p] = static_cast<int32_t>(p);
-}
-
-// sorted[i] = the nonzero p at staging slot i (stable by p within a block)
-__global__ void k_fill_map(const int32_t* __restrict__ sorted, const int32_t* __restrict__ pos, int32_t nnz,
-                           int32_t* __restrict__ dest, uint16_t* __restrict__ local) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= nnz) return;
-  const int32_t p = sorted[i];
-  dest[p] = static_cast<int32_t>(i);
-  local[i] = static_cast<uint16_t>(static_cast<uint32_t>(pos[p]) % SPX_CSC_BLOCK);
+__global__ __launch_bounds__(kMapThreads) void k_block_map(const int32_t* __restrict__ perm, int32_t nnz, int bits,
+                                                           int32_t* __restrict__ dest, uint16_t* __restrict__ local) {
+  __shared__ int32_t s_p[SPX_CSC_BLOCK];
+  __shared__ uint16_t s_i[SPX_CSC_BLOCK];
+  __shared__ uint16_t s_cnt[kMapWaves][256];
+  __shared__ int32_t s_wsum[256 / kWave];
+  const int t = threadIdx.x, lane = t % kWave, w = t / kWave;
+  const uint64_t lt_mask = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
+  const int64_t b0 = static_cast<int64_t>(blockIdx.x) * SPX_CSC_BLOCK;
+  const int64_t left = static_cast<int64_t>(nnz) - b0;
+  const int32_t here = static_cast<int32_t>(left < SPX_CSC_BLOCK ? left : SPX_CSC_BLOCK);
+  int32_t p[kMapItems];
+  uint16_t at[kMapItems];
+#pragma unroll
+  for (int j = 0; j < kMapItems; ++j) {
+    const int i = w * (SPX_CSC_BLOCK / kMapWaves) + j * kWave + lane;
+    at[j] = static_cast<uint16_t>(i);
+    p[j] = i < here ? perm[b0 + i] : 0;
+  }
+  for (int shift = 0; shift < bits; shift += 8) {
+    for (int i = t; i < kMapWaves * 256; i += kMapThreads) (&s_cnt[0][0])[i] = 0;
+    __syncthreads();
+    uint16_t rank[kMapItems];
+    volatile uint16_t* cnt = s_cnt[w];
+#pragma unroll
+    for (int j = 0; j < kMapItems; ++j) {
+      const bool valid = w * (SPX_CSC_BLOCK / kMapWaves) + j * kWave + lane < here;
+      const uint32_t d = (static_cast<uint32_t>(p[j]) >> shift) & 255u;
+      uint64_t peers = __ballot(valid);
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const uint64_t bal = __ballot(bit);
+        peers &= bit ? bal : ~bal;
+      }
+      const int r = __popcll(peers & lt_mask);
+      const uint16_t old = cnt[d];
+      rank[j] = static_cast<uint16_t>(old + r);
+      if (valid && r == 0) cnt[d] = static_cast<uint16_t>(old + __popcll(peers));
+    }
+    __syncthreads();
+    int32_t run = 0, inc = 0;
+    if (t < 256) {  // thread t: digit t
+      for (int v = 0; v < kMapWaves; ++v) {
+        const int32_t c = s_cnt[v][t];
+        s_cnt[v][t] = static_cast<uint16_t>(run);
+        run += c;
+      }
+      inc = radix::wave_incl_scan(run, lane);
+      if (lane == kWave - 1) s_wsum[w] = inc;
+    }
+    __syncthreads();
+    if (t < 256) {
+      int32_t start = inc - run;
+      for (int v = 0; v < w; ++v) start += s_wsum[v];
+      for (int v = 0; v < kMapWaves; ++v) s_cnt[v][t] = static_cast<uint16_t>(s_cnt[v][t] + start);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kMapItems; ++j) {
+      if (w * (SPX_CSC_BLOCK / kMapWaves) + j * kWave + lane >= here) continue;
+      const int to = rank[j] + s_cnt[w][(static_cast<uint32_t>(p[j]) >> shift) & 255u];
+      s_p[to] = p[j];
+      s_i[to] = at[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kMapItems; ++j) {
+      const int i = w * (SPX_CSC_BLOCK / kMapWaves) + j * kWave + lane;
+      if (i < here) {
+        p[j] = s_p[i];
+        at[j] = s_i[i];
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < kMapItems; ++j) {
+    const int i = w * (SPX_CSC_BLOCK / kMapWaves) + j * kWave + lane;
+    if (i >= here) continue;
+    if (p[j] >= 0 && p[j] < nnz) dest[p[j]] = static_cast<int32_t>(b0 + i);
+    local[b0 + i] = at[j];
+  }
 }
 
 // Pass 1 tiles are XCD-contiguous (grid a multiple of 8): XCD j streams one
@@ -681,8 +752,6 @@ __global__ __launch_bounds__(kWG) void k_from_staging(const T* __restrict__ stag
   for (int32_t i = threadIdx.x; i < cnt; i += kWG) __builtin_nontemporal_store(blk[i], out + b0 + i);
 }
 
-unsigned grid256(int64_t n) { return static_cast<unsigned>((n + 255) / 256); }
-
 int bits_for(int64_t v) {
   int b = 1;
   while ((int64_t(1) << b) <= v) ++b;
@@ -696,8 +765,7 @@ using namespace spx;
 
 extern "C" spx_status csr_csc_value_map_workspace_bytes(int32_t nnz, size_t* bytes) {
   if (!bytes || nnz < 0) return fail(SPX_ERR_INVALID, "csr_csc_value_map_workspace_bytes: bad argument");
-  const size_t n = static_cast<size_t>(nnz > 0 ? nnz : 1);
-  *bytes = 3 * align_up(n * 4) + radix_workspace_bytes(nnz, 4);
+  *bytes = 256;  // the map is built in LDS
   return SPX_OK;
 }
 
@@ -715,20 +783,9 @@ extern "C" spx_status csr_csc_value_map(int32_t nnz, const int32_t* perm, int32_
   if (!workspace || ws_bytes < need)
     return fail(SPX_ERR_WORKSPACE, "csr_csc_value_map: workspace %zu < %zu bytes", ws_bytes, need);
   hipStream_t st = as_stream(stream);
-  char* w = static_cast<char*>(workspace);
-  const size_t n4 = align_up(static_cast<size_t>(nnz) * 4);
-  int32_t* pos = reinterpret_cast<int32_t*>(w);
-  uint32_t* keys = reinterpret_cast<uint32_t*>(w + n4);
-  int32_t* vals = reinterpret_cast<int32_t*>(w + 2 * n4);
-  void* rws = w + 3 * n4;
-  k_inv_perm<<<grid256(nnz), 256, 0, st>>>(perm, nnz, pos);
-  SPX_LAUNCHED("k_inv_perm");
-  k_block_keys<<<grid256(nnz), 256, 0, st>>>(pos, nnz, keys, vals);
-  SPX_LAUNCHED("k_block_keys");
-  const spx_status s = radix_sort_u32(keys, vals, nnz, bits_for((static_cast<int64_t>(nnz) - 1) / SPX_CSC_BLOCK), rws, st);
-  if (s != SPX_OK) return s;
-  k_fill_map<<<grid256(nnz), 256, 0, st>>>(vals, pos, nnz, dest, local);
-  SPX_LAUNCHED("k_fill_map");
+  const unsigned nb = static_cast<unsigned>((static_cast<int64_t>(nnz) + SPX_CSC_BLOCK - 1) / SPX_CSC_BLOCK);
+  k_block_map<<<nb, kMapThreads, 0, st>>>(perm, nnz, bits_for(static_cast<int64_t>(nnz) - 1), dest, local);
+  SPX_LAUNCHED("k_block_map");
   return SPX_OK;
 }
 

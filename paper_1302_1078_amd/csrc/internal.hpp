@@ -61,7 +61,7 @@ struct Carve {
 };
 
 // ------------------------------------------------------------------ device primitives
-// (scan_sort.hip)
+// (scan.hip; the radix sort is radix.hpp)
 
 constexpr int kScanTile = 4096;  // 256 threads x 16 items
 
@@ -70,14 +70,6 @@ constexpr int kScanTile = 4096;  // 256 threads x 16 items
 size_t scan_workspace_bytes(int64_t n);
 spx_status exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* total,
                               void* ws, hipStream_t st);
-
-// Stable LSD radix sort of (key, value) pairs on the low `bits` bits of the
-// key.  keys/vals are sorted in place (ping-pong buffers come from ws).
-size_t radix_workspace_bytes(int64_t n, int key_bytes);
-spx_status radix_sort_u32(uint32_t* keys, int32_t* vals, int64_t n, int bits, void* ws,
-                          hipStream_t st);
-spx_status radix_sort_u64(uint64_t* keys, int32_t* vals, int64_t n, int bits, void* ws,
-                          hipStream_t st);
 
 // ------------------------------------------------------------------ products
 

@@ -21,6 +21,7 @@
 
 #include "device.hpp"
 #include "internal.hpp"
+#include "radix.hpp"
 
 namespace spx {
 namespace {
@@ -261,19 +262,33 @@ __global__ void k_invert(const int32_t* __restrict__ perm, int32_t m, int32_t* _
   if (o >= 0 && o < m) inv[o] = static_cast<int32_t>(i);
 }
 
-// One thread per old row: its triplets keep their positions, with both
-// indices renamed (a row or column whose label is missing stays -1 and is
-// reported by the assembly's range check).
-__global__ void k_relabel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
-                          const double* __restrict__ values, const int32_t* __restrict__ inv, int32_t m,
-                          int32_t* __restrict__ r, int32_t* __restrict__ c, double* __restrict__ v) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  const int32_t ri = inv[i];
-  for (int32_t p = rowptr[i]; p < rowptr[i + 1]; ++p) {
-    r[p] = ri;
-    c[p] = inv[colind[p]];
-    v[p] = values[p];
+// The nonzeros keep their positions, with both indices renamed (a row or
+// column whose label is missing stays -1 and is reported by the assembly's
+// range check).  Tiles of consecutive nonzeros, so a row's length does not
+// matter: with a thread per row, the longest row of a power law (20,000 of
+// 4.8 M nonzeros) alone held the kernel for 4.9 ms; this takes 33 us.
+__global__ __launch_bounds__(kWG) void k_relabel(const int32_t* __restrict__ rowptr,
+                                                 const int32_t* __restrict__ colind,
+                                                 const int32_t* __restrict__ inv, int32_t m, int32_t nnz,
+                                                 int32_t* __restrict__ r, int32_t* __restrict__ c) {
+  __shared__ int32_t s_row[radix::kTile];
+  __shared__ int32_t s_wsum[radix::kWaves];
+  const int t = threadIdx.x, lane = t % kWave, w = t / kWave;
+  const int32_t base = static_cast<int32_t>(blockIdx.x) * radix::kTile;
+  const int32_t here = min(radix::kTile, nnz - base);
+  int32_t col[radix::kItems], row[radix::kItems];
+#pragma unroll
+  for (int j = 0; j < radix::kItems; ++j) {
+    const int32_t i = w * (radix::kTile / radix::kWaves) + j * kWave + lane;
+    if (i < here) col[j] = colind[base + i];
+  }
+  radix::tile_rows(rowptr, m, base, here, s_row, s_wsum, row);
+#pragma unroll
+  for (int j = 0; j < radix::kItems; ++j) {
+    const int32_t i = w * (radix::kTile / radix::kWaves) + j * kWave + lane;
+    if (i >= here) continue;
+    r[base + i] = inv[row[j]];
+    c[base + i] = inv[col[j]];
   }
 }
 
@@ -288,14 +303,97 @@ __global__ void k_col_count(const int32_t* __restrict__ colind, int64_t nnz, int
   if (c >= 0 && c < n) atomicAdd(cnt + c, 1);
 }
 
-// Sort keys: the complemented count, so an ascending stable sort lists
-// columns by descending count with ties in ascending index; values = index.
-__global__ void k_degree_keys(const int32_t* __restrict__ cnt, int32_t n, uint32_t* __restrict__ keys,
-                              int32_t* __restrict__ idx) {
-  const int64_t j = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  keys[j] = ~static_cast<uint32_t>(cnt[j]);
-  idx[j] = static_cast<int32_t>(j);
+// The same from columns grouped by their high bits (one radix pass), so that a
+// tile holds few distinct columns: it counts them in LDS and adds each count
+// with one atomic.  Every global atomic is performed past L2, and those of a
+// column follow one another; on a power law the hot columns' repeats are most
+// of them (4.8 M nonzeros: 289 us with an atomic each, 62 us with the pass).
+constexpr int kCountWindow = 4096;       // columns counted in LDS, from the tile's first group on
+constexpr int64_t kGroupedCount = 1 << 17;  // nonzeros from which the pass over the columns pays for itself
+
+struct ColKeySrc {
+  const int32_t* colind;
+  __device__ __forceinline__ uint32_t raw(int64_t i) const { return static_cast<uint32_t>(colind[i]); }
+  __device__ __forceinline__ uint32_t key(uint32_t x) const { return x; }
+  __device__ __forceinline__ void check(uint32_t) const {}
+  __device__ __forceinline__ radix::NoVal val(int64_t) const { return radix::NoVal(); }
+};
+
+struct KeySink {
+  uint32_t* k;
+  __device__ __forceinline__ void put_key(int64_t i, uint32_t x) const { k[i] = x; }
+};
+
+__global__ __launch_bounds__(kWG) void k_col_count_grouped(const uint32_t* __restrict__ grouped, int64_t nnz,
+                                                           int32_t n, int shift, uint32_t mask,
+                                                           int32_t* __restrict__ cnt) {
+  __shared__ int32_t s_cnt[kCountWindow];
+  const int t = threadIdx.x;
+  const int64_t base = static_cast<int64_t>(blockIdx.x) * radix::kTile;
+  for (int i = t; i < kCountWindow; i += kWG) s_cnt[i] = 0;
+  const uint32_t first = ((grouped[base] >> shift) & mask) << shift;  // of a column inside [0, n): its group
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < radix::kItems; ++j) {
+    const int64_t i = base + j * kWG + t;
+    if (i >= nnz) continue;
+    const uint32_t c = grouped[i];
+    if (c >= static_cast<uint32_t>(n)) continue;
+    if (c - first < static_cast<uint32_t>(kCountWindow)) atomicAdd(&s_cnt[c - first], 1);
+    else atomicAdd(cnt + c, 1);
+  }
+  __syncthreads();
+  for (int i = t; i < kCountWindow; i += kWG)
+    if (s_cnt[i]) atomicAdd(cnt + first + i, s_cnt[i]);
+}
+
+// Columns by their complemented count: an ascending stable sort lists them by
+// descending count with ties in ascending index.
+struct DegreeSrc {
+  const int32_t* cnt;
+  uint32_t top;
+  __device__ __forceinline__ int32_t raw(int64_t j) const { return cnt[j]; }
+  __device__ __forceinline__ uint32_t key(int32_t x) const { return top - static_cast<uint32_t>(x); }
+  __device__ __forceinline__ void check(int32_t) const {}
+  __device__ __forceinline__ int32_t val(int64_t j) const { return static_cast<int32_t>(j); }
+};
+
+struct PermSink {
+  int32_t* perm;
+  __device__ __forceinline__ void put_key(int64_t, uint32_t) const {}
+  __device__ __forceinline__ void put_val(int64_t i, int32_t x) const { perm[i] = x; }
+};
+
+int bits_for(int64_t x) {  // bits needed to represent x >= 0
+  int b = 0;
+  while (x > 0) {
+    ++b;
+    x >>= 1;
+  }
+  return b;
+}
+
+struct DegreeWs {
+  int32_t* cnt;
+  uint32_t* keys[2];
+  int32_t* vals[2];
+  uint32_t* grouped;
+  void* radix;
+};
+
+DegreeWs carve_degree(void* ws, int32_t n, int32_t nnz, size_t* bytes) {
+  Carve cv(ws, ~size_t(0));
+  const int64_t e = n > 0 ? n : 1;
+  DegreeWs w;
+  w.cnt = cv.take<int32_t>(e);
+  for (int i = 0; i < 2; ++i) {
+    w.keys[i] = cv.take<uint32_t>(e);
+    w.vals[i] = cv.take<int32_t>(e);
+  }
+  w.grouped = cv.take<uint32_t>(nnz >= kGroupedCount ? nnz : 1);
+  w.radix = cv.take<char>(radix::count_bytes(nnz > n ? nnz : n));
+  *bytes = cv.used;
+  return w;
 }
 
 // Bandwidth (Sec. 4.4): max |colind[p] - r| over the nonzeros of each row r;
@@ -322,7 +420,7 @@ __global__ void k_bandwidth(const int32_t* __restrict__ rowptr, const int32_t* _
 
 extern "C" spx_status csr_degree_order_workspace_bytes(int32_t n, int32_t nnz, size_t* bytes) {
   if (!bytes || n < 0 || nnz < 0) return fail(SPX_ERR_INVALID, "csr_degree_order_workspace_bytes: bad argument");
-  *bytes = 2 * align256(sizeof(int32_t) * static_cast<size_t>(n > 0 ? n : 1)) + radix_workspace_bytes(n, 4);
+  carve_degree(nullptr, n, nnz, bytes);
   return SPX_OK;
 }
 
@@ -341,20 +439,25 @@ extern "C" spx_status csr_degree_order(int32_t n, int32_t nnz, const int32_t* co
     return fail(SPX_ERR_WORKSPACE, "csr_degree_order: workspace %zu < %zu bytes", ws_bytes, need);
   if (n == 0) return SPX_OK;
   hipStream_t st = as_stream(stream);
-  char* w = static_cast<char*>(workspace);
-  int32_t* cnt = reinterpret_cast<int32_t*>(w);
-  w += align256(sizeof(int32_t) * static_cast<size_t>(n));
-  uint32_t* keys = reinterpret_cast<uint32_t*>(w);
-  w += align256(sizeof(int32_t) * static_cast<size_t>(n));
-  k_set_i32<<<blocks_for(n), 256, 0, st>>>(cnt, n, 0);
+  const DegreeWs w = carve_degree(workspace, n, nnz, &need);
+  k_set_i32<<<blocks_for(n), 256, 0, st>>>(w.cnt, n, 0);
   SPX_LAUNCHED("k_set_i32");
-  if (nnz > 0) {
-    k_col_count<<<blocks_for(nnz), 256, 0, st>>>(colind, nnz, n, cnt);
+  if (nnz >= kGroupedCount) {
+    const int bits = bits_for(n - 1);
+    const int width = bits < radix::kMaxDigit ? bits : radix::kMaxDigit, shift = bits - width;
+    s = radix::pass(ColKeySrc{colind}, KeySink{w.grouped}, nnz, shift, width, w.radix, st);
+    if (s != SPX_OK) return s;
+    k_col_count_grouped<<<static_cast<unsigned>(radix::tiles_of(nnz)), kWG, 0, st>>>(
+        w.grouped, nnz, n, shift, (1u << width) - 1u, w.cnt);
+    SPX_LAUNCHED("k_col_count_grouped");
+  } else if (nnz > 0) {
+    k_col_count<<<blocks_for(nnz), 256, 0, st>>>(colind, nnz, n, w.cnt);
     SPX_LAUNCHED("k_col_count");
   }
-  k_degree_keys<<<blocks_for(n), 256, 0, st>>>(cnt, n, keys, perm);
-  SPX_LAUNCHED("k_degree_keys");
-  return radix_sort_u32(keys, perm, n, 32, w, st);
+  // a count is at most nnz, so its complement needs no more bits than nnz
+  const int bits = bits_for(nnz);
+  const radix::Pairs<uint32_t, int32_t> a{w.keys[0], w.vals[0]}, b{w.keys[1], w.vals[1]};
+  return radix::sort(DegreeSrc{w.cnt, (1u << bits) - 1u}, a, b, PermSink{perm}, n, bits, w.radix, st);
 }
 
 extern "C" spx_status csr_permute_workspace_bytes(int32_t m, int32_t nnz, size_t* bytes) {
@@ -362,8 +465,7 @@ extern "C" spx_status csr_permute_workspace_bytes(int32_t m, int32_t nnz, size_t
   size_t coo = 0;
   spx_status s = csr_from_coo_workspace_bytes(m, m, nnz, &coo);
   if (s != SPX_OK) return s;
-  *bytes = align256(sizeof(int32_t) * static_cast<size_t>(m)) + 2 * align256(sizeof(int32_t) * static_cast<size_t>(nnz)) +
-           align256(sizeof(double) * static_cast<size_t>(nnz)) + coo;
+  *bytes = align256(sizeof(int32_t) * static_cast<size_t>(m)) + 2 * align256(sizeof(int32_t) * static_cast<size_t>(nnz)) + coo;
   return SPX_OK;
 }
 
@@ -392,17 +494,17 @@ extern "C" spx_status csr_permute(int32_t m, int32_t nnz, const int32_t* rowptr,
   w += align256(sizeof(int32_t) * static_cast<size_t>(nnz));
   int32_t* c = reinterpret_cast<int32_t*>(w);
   w += align256(sizeof(int32_t) * static_cast<size_t>(nnz));
-  double* v = reinterpret_cast<double*>(w);
-  w += align256(sizeof(double) * static_cast<size_t>(nnz));
   if (m > 0) {
     k_set_i32<<<blocks_for(m), 256, 0, st>>>(inv, m, -1);
     SPX_LAUNCHED("k_set_i32");
     k_invert<<<blocks_for(m), 256, 0, st>>>(perm, m, inv);
     SPX_LAUNCHED("k_invert");
-    k_relabel<<<blocks_for(m), 256, 0, st>>>(rowptr, colind, values, inv, m, r, c, v);
-    SPX_LAUNCHED("k_relabel");
+    if (nnz > 0) {
+      k_relabel<<<static_cast<unsigned>(radix::tiles_of(nnz)), kWG, 0, st>>>(rowptr, colind, inv, m, nnz, r, c);
+      SPX_LAUNCHED("k_relabel");
+    }
   }
-  return csr_from_coo(m, m, nnz, r, c, v, rowptr_out, colind_out, values_out, nnz_out, w,
+  return csr_from_coo(m, m, nnz, r, c, values, rowptr_out, colind_out, values_out, nnz_out, w,
                       ws_bytes - static_cast<size_t>(w - static_cast<char*>(workspace)), stream);
 }
 
