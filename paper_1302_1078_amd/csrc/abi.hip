@@ -46,6 +46,15 @@ void layout_for_k(int32_t k, spx_dtype xt, const void* X, int64_t ldx, const voi
   *kl = l;
 }
 
+void layout_any_stride(int32_t k, spx_dtype xt, uint32_t flags, int* kl, int* vec) {
+  const int V = (xt == SPX_F64) ? 2 : 4;
+  *vec = (k >= V && !(flags & SPX_FLAG_SCALAR_X)) ? V : 1;
+  const int per = (k + *vec - 1) / *vec;
+  int l = 1;
+  while (l < per && l < 32) l <<= 1;
+  *kl = l;
+}
+
 namespace {
 
 bool pair_ok(spx_dtype vt, spx_dtype xt) {
@@ -98,11 +107,12 @@ spx_status product(const char* who, int32_t m, int32_t n, int32_t nnz, const int
   a.ldy = ldy;
   a.k = k;
   int kl, vec;
-  layout_for_k(k, xt, X, a.ldx, Y, a.ldy, plan ? plan->opts.flags : 0u, &kl, &vec);
   if (plan && plan->staged) {
+    layout_for_k(k, xt, X, a.ldx, Y, a.ldy, plan->opts.flags, &kl, &vec);
     if (vperm) return fail(SPX_ERR_UNSUPPORTED, "%s: a staged plan serves CSR-order values only", who);
     return launch_staged(a, plan, m, vt, xt, kl, vec, as_stream(stream));
   }
+  layout_any_stride(k, xt, plan ? plan->opts.flags : 0u, &kl, &vec);
   if (plan) bins_from_plan(plan, a, kl, true);
   else bins_unbinned(m, nnz, kl, a);
   if (xsave) {

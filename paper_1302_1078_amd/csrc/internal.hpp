@@ -170,6 +170,15 @@ void bins_from_plan(const spx_plan* plan, ProdArgs& a, int kl, bool own_launch);
 void bins_unbinned(int32_t m, int32_t nnz, int kl, ProdArgs& a);
 int lanes_valid(int lanes);
 // Lanes per X row (KL) and elements per lane (VEC) for k right-hand sides.
+// layout_for_k: VEC > 1 only where every lane's access is a whole, aligned 16
+// bytes (k and both leading dimensions multiples of it).
+// layout_any_stride: VEC elements wherever a row has as many.  The memory
+// unit takes 16-byte accesses at any element-aligned address, and the last
+// lane of a row takes the row's last VEC elements, overlapping its neighbour
+// (lane_col in product_impl.hpp).  Scalar lanes need up to VEC times as many
+// lanes and addresses per nonzero: k = 5, FP32 vectors, 2.4 M nonzeros took
+// 38 us with 8 scalar lanes.
+void layout_any_stride(int32_t k, spx_dtype xt, uint32_t flags, int* kl, int* vec);
 void layout_for_k(int32_t k, spx_dtype xt, const void* X, int64_t ldx, const void* Y, int64_t ldy,
                   uint32_t flags, int* kl, int* vec);
 // Product through a staged plan (staged.hip).

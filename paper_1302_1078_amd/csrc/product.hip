@@ -87,6 +87,22 @@ __global__ __launch_bounds__(kWG) void k_product(const ProdArgs a) {
   }
 }
 
+// A product without a plan: one bin of natural-order rows.
+template <class C>
+__global__ __launch_bounds__(kWG) void k_product_free(const ProdArgs a) {
+  const BinDesc d = a.bins[0];
+  const int tile = xcd_tile(blockIdx.x, d.nblk);
+  switch (d.lanes) {
+    case 1: do_rows_free<C, 1>(a, d, tile); break;
+    case 2: do_rows_free<C, 2>(a, d, tile); break;
+    case 4: do_rows_free<C, 4>(a, d, tile); break;
+    case 8: do_rows_free<C, 8>(a, d, tile); break;
+    case 16: do_rows_free<C, 16>(a, d, tile); break;
+    case 32: do_rows_free<C, 32>(a, d, tile); break;
+    default: do_rows_free<C, 64>(a, d, tile); break;
+  }
+}
+
 // Dynamic LDS that lets at most `occ` workgroups of kernel `fn` share a CU
 // (each workgroup then holds more than 1/(occ+1) of the CU's LDS).
 spx_status occupancy_lds(const void* fn, int occ, size_t* dyn) {
@@ -109,6 +125,14 @@ spx_status occupancy_lds(const void* fn, int occ, size_t* dyn) {
 
 template <class C, bool MR>
 spx_status launch_k(const ProdArgs& a, unsigned grid, hipStream_t st) {
+  if (!a.row_perm) {
+    if constexpr (!C::kHot && !MR) {  // no plan: one bin of one row per group
+      k_product_free<C><<<grid, kWG, 0, st>>>(a);
+      SPX_LAUNCHED("k_product_free");
+      return SPX_OK;
+    }
+    return fail(SPX_ERR_INVALID, "product: a plan without rows");
+  }
   size_t dyn = 0;
   if (a.occupancy > 0) {
     const spx_status s = occupancy_lds(reinterpret_cast<const void*>(&k_product<C, MR>), a.occupancy, &dyn);

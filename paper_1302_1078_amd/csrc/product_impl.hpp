@@ -52,14 +52,27 @@ struct Cfg {
 template <typename T, int N>
 struct VecT {
   typedef T type __attribute__((ext_vector_type(N)));
+  // the same at any element-aligned address (rows of X and Y)
+  typedef T any __attribute__((ext_vector_type(N), aligned(sizeof(T))));
 };
+
+// First column of lane kl in the slab that starts at column c0: the last lane
+// of a row whose k is no multiple of VEC takes the row's last VEC elements
+// again (every lane's sums are complete, so shared columns hold equal bits).
+// Lanes past the row (column >= k) do nothing.
+template <int VEC>
+__device__ __forceinline__ int lane_col(int32_t k, int c0, int kl) {
+  const int col = c0 + kl * VEC;
+  if constexpr (VEC > 1) return col < k ? min(col, k - VEC) : col;
+  else return col;
+}
 
 template <typename T, int N>
 __device__ __forceinline__ void load_x(const T* p, T (&out)[N]) {
   if constexpr (N == 1) {
     out[0] = *p;
   } else {
-    typedef typename VecT<T, N>::type V;
+    typedef typename VecT<T, N>::any V;
     V v = *reinterpret_cast<const V*>(p);
 #pragma unroll
     for (int i = 0; i < N; ++i) out[i] = v[i];
@@ -86,7 +99,7 @@ __device__ __forceinline__ void store_y(T* p, const T (&in)[N], bool nt) {
   if constexpr (N == 1) {
     if (nt) __builtin_nontemporal_store(in[0], p); else *p = in[0];
   } else {
-    typedef typename VecT<T, N>::type V;
+    typedef typename VecT<T, N>::any V;
     V v;
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = in[i];
@@ -133,13 +146,12 @@ __device__ __forceinline__ void save_x(const ProdArgs& a, int32_t p, typename C:
 // them through ds_bpermute, so a round costs the texture addresser U lanes
 // of index loads instead of U x KL (the address unit, not HBM, bounds the
 // short-row SpMM).
-template <class C, int S>
+template <class C, int S, int U = C::U>
 __device__ __forceinline__ void accumulate(const ProdArgs& a, int32_t p0, int32_t p1, int slot,
                                            int col, bool comp, typename C::AT (&acc)[C::VEC],
                                            Comp (&cacc)[C::VEC]) {
   using XT = typename C::XT;
   constexpr int VEC = C::VEC;
-  constexpr int U = C::U;
   const XT* X = static_cast<const XT*>(a.X) + col;
   const int64_t ldx = a.ldx;
   const bool colok = col < a.k;
@@ -254,6 +266,49 @@ __device__ __forceinline__ void finish_small(const ProdArgs& a, bool active, boo
   }
 }
 
+// Sum over the slots of a whole workgroup (every thread holds a partial sum of
+// the same row) and store the row's VEC outputs: waves reduce, then LDS across
+// the 4 waves.
+template <class C>
+__device__ __forceinline__ void finish_workgroup(const ProdArgs& a, bool comp, int col, int32_t row,
+                                                 typename C::AT (&acc)[C::VEC], Comp (&cacc)[C::VEC], bool nt) {
+  constexpr int KL = C::KL, VEC = C::VEC;
+  using XT = typename C::XT;
+  using AT = typename C::AT;
+  const int t = threadIdx.x;
+  __shared__ double red[kWG / kWave][KL][VEC];
+  const int w = t / kWave;
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    double v;
+    if constexpr (C::kComp) {
+      v = comp ? group_sum<kWave, KL>(cacc[e].value())
+               : static_cast<double>(group_sum<kWave, KL>(acc[e]));
+    } else {
+      v = group_sum<kWave, KL>(acc[e]);
+    }
+    if ((t % kWave) < KL) red[w][t % kWave][e] = v;
+  }
+  __syncthreads();
+  if (t < KL && col < a.k) {
+    XT out[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      if (C::kComp && comp) {
+        double s = 0.0;
+        for (int i = 0; i < kWG / kWave; ++i) s += red[i][t][e];
+        out[e] = static_cast<XT>(s);
+      } else {
+        AT s = AT(0);
+        for (int i = 0; i < kWG / kWave; ++i) s += static_cast<AT>(red[i][t][e]);
+        out[e] = s;
+      }
+    }
+    store_y<XT, VEC>(static_cast<XT*>(a.Y) + static_cast<int64_t>(row) * a.ldy + col, out, nt);
+  }
+  __syncthreads();
+}
+
 // Row groups of G threads (G in 1..64 or 256), R rows per group.
 //  R == 1: the group walks its row with U independent nonzeros per lane.
 //  R > 1 (short-row bins, at most one nonzero per slot and row): the group
@@ -289,7 +344,7 @@ __device__ __forceinline__ void do_rows(const ProdArgs& a, const BinDesc& d, int
       if (active[j]) row_range(a, d, idx, row[j], p0[j], p1[j]);
     }
     for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
-      const int col = c0 + kl * VEC;
+      const int col = lane_col<VEC>(a.k, c0, kl);
       const XT* X = static_cast<const XT*>(a.X) + col;
       int32_t c[R];
       XT v[R];
@@ -367,10 +422,8 @@ __device__ __forceinline__ void do_rows(const ProdArgs& a, const BinDesc& d, int
       row_range(a, d, idx, row, p0, p1);
     }
     const bool comp = C::kComp && (p1 - p0 > a.kahan_len);
-    XT* Y = static_cast<XT*>(a.Y);
-
     for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
-      const int col = c0 + kl * VEC;
+      const int col = lane_col<VEC>(a.k, c0, kl);
       AT acc[VEC];
       Comp cacc[VEC];
 #pragma unroll
@@ -383,39 +436,75 @@ __device__ __forceinline__ void do_rows(const ProdArgs& a, const BinDesc& d, int
       if constexpr (GG <= kWave) {
         finish_small<C, GG>(a, active, comp, slot, col, row, acc, cacc, nt);
       } else {
-        // one row per workgroup: waves reduce, then LDS across the 4 waves
-        __shared__ double red[kWG / kWave][KL][VEC];
-        const int w = t / kWave;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          double v;
-          if constexpr (C::kComp) {
-            v = comp ? group_sum<kWave, KL>(cacc[e].value())
-                     : static_cast<double>(group_sum<kWave, KL>(acc[e]));
-          } else {
-            v = group_sum<kWave, KL>(acc[e]);
-          }
-          if ((t % kWave) < KL) red[w][t % kWave][e] = v;
-        }
-        __syncthreads();
-        if (t < KL && col < a.k) {
-          XT out[VEC];
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) {
-            if (C::kComp && comp) {
-              double s = 0.0;
-              for (int i = 0; i < kWG / kWave; ++i) s += red[i][t][e];
-              out[e] = static_cast<XT>(s);
-            } else {
-              AT s = AT(0);
-              for (int i = 0; i < kWG / kWave; ++i) s += static_cast<AT>(red[i][t][e]);
-              out[e] = s;
-            }
-          }
-          store_y<XT, VEC>(Y + static_cast<int64_t>(row) * a.ldy + col, out, nt);
-        }
-        __syncthreads();
+        finish_workgroup<C>(a, comp, col, row, acc, cacc, nt);
       }
+    }
+  }
+}
+
+// Without a plan (rows in natural order, one group size for all): groups of G
+// threads serve the rows, and a row that would take a group more than
+// kFreeRounds rounds is left to the whole workgroup, which comes back to its
+// long rows one after the other with free_unroll nonzeros in flight per lane.
+// The longest row bounds the launch: a group of 8 lanes needs 5,000 dependent
+// rounds for 20,000 nonzeros and k = 5.
+constexpr int kFreeRounds = 8;
+template <class C>  // eight 16-byte rows of X would cost every row's occupancy (8 to 5 waves per SIMD)
+constexpr int free_unroll() {
+  return C::VEC == 1 ? 8 : 4;
+}
+
+template <class C, int G>
+__device__ __forceinline__ void do_rows_free(const ProdArgs& a, const BinDesc& d, int tile) {
+  constexpr int KL = C::KL, VEC = C::VEC;
+  constexpr int S = (G >= KL) ? G / KL : 1;
+  constexpr int GG = S * KL;
+  constexpr int NG = kWG / GG;
+  static_assert(GG <= kWave, "groups inside one wavefront");
+  __shared__ int32_t s_long[NG];
+  __shared__ int32_t s_nlong;
+  if (tile * NG >= d.nrows) return;  // whole workgroup idle (uniform)
+  const int t = threadIdx.x;
+  const int ln = t % GG, slot = ln / KL, kl = ln % KL;
+  const bool nt = !(a.flags & SPX_FLAG_NO_NT_STORE);
+  if (t == 0) s_nlong = 0;
+  __syncthreads();
+  const int idx = tile * NG + t / GG;
+  const bool active = idx < d.nrows;
+  int32_t row = 0, p0 = 0, p1 = 0;
+  if (active) row_range(a, d, idx, row, p0, p1);
+  const bool later = p1 - p0 > kFreeRounds * C::U * S;
+  if (later) {
+    if (ln == 0) s_long[atomicAdd(&s_nlong, 1)] = row;
+    p1 = p0;
+  }
+  typename C::AT acc[VEC];
+  Comp cacc[VEC];
+  auto clear = [&]() {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      acc[e] = 0;
+      cacc[e].init();
+    }
+  };
+  const bool comp = C::kComp && (p1 - p0 > a.kahan_len);
+  for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
+    const int col = lane_col<VEC>(a.k, c0, kl);
+    clear();
+    accumulate<C, S>(a, p0, p1, slot, col, comp, acc, cacc);
+    finish_small<C, GG>(a, active && !later, comp, slot, col, row, acc, cacc, nt);
+  }
+  __syncthreads();
+  const int32_t n = __builtin_amdgcn_readfirstlane(s_nlong);
+  for (int32_t i = 0; i < n; ++i) {
+    const int32_t r = __builtin_amdgcn_readfirstlane(s_long[i]);
+    const int32_t q0 = a.rowptr[r], q1 = a.rowptr[r + 1];
+    const bool lcomp = C::kComp && (q1 - q0 > a.kahan_len);
+    for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
+      const int col = lane_col<VEC>(a.k, c0, t % KL);
+      clear();
+      accumulate<C, kWG / KL, free_unroll<C>()>(a, q0, q1, t / KL, col, lcomp, acc, cacc);
+      finish_workgroup<C>(a, lcomp, col, r, acc, cacc, nt);
     }
   }
 }
@@ -667,7 +756,7 @@ __device__ __forceinline__ void do_split(const ProdArgs& a, const BinDesc& d, in
   double* part = a.partials + static_cast<int64_t>(tile) * a.max_k;
 
   for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
-    const int col = c0 + kl * VEC;
+    const int col = lane_col<VEC>(a.k, c0, kl);
     AT acc[VEC];
     Comp cacc[VEC];
 #pragma unroll
