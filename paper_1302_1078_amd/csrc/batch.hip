@@ -47,50 +47,6 @@ struct BatchArgs {
 // layouts: 0 -> (KL 1, VEC 1); i >= 1 -> (KL 2^(i-1), VEC V)
 constexpr int kLayouts = 7;
 
-template <class C, bool MR>
-__device__ __forceinline__ void run_tile(const ProdArgs& a, const BinDesc& d, int tile) {
-  constexpr bool kMulti = MR && C::KL == 1 && C::VEC == 1;
-  switch (d.lanes + (d.rpg > 1 ? 1000 : 0)) {
-    case 1: do_rows<C, 1, 1>(a, d, tile); break;
-    case 2: do_rows<C, 2, 1>(a, d, tile); break;
-    case 4: do_rows<C, 4, 1>(a, d, tile); break;
-    case 8: do_rows<C, 8, 1>(a, d, tile); break;
-    case 16: do_rows<C, 16, 1>(a, d, tile); break;
-    case 32: do_rows<C, 32, 1>(a, d, tile); break;
-    case 64: do_rows<C, 64, 1>(a, d, tile); break;
-    case 256: do_rows<C, 256, 1>(a, d, tile); break;
-    case 1001:
-      if constexpr (kMulti) do_rows<C, 1, 4>(a, d, tile);
-      else do_rows<C, 1, 1>(a, d, tile);
-      break;
-    case 1002:
-      if constexpr (kMulti) do_rows<C, 2, 4>(a, d, tile);
-      else do_rows<C, 2, 1>(a, d, tile);
-      break;
-    case 1004:
-      if constexpr (kMulti) do_rows<C, 4, 4>(a, d, tile);
-      else do_rows<C, 4, 1>(a, d, tile);
-      break;
-    case 1008:
-      if constexpr (kMulti) do_rows<C, 8, 4>(a, d, tile);
-      else do_rows<C, 8, 1>(a, d, tile);
-      break;
-    case 1016:
-      if constexpr (kMulti) do_rows<C, 16, 4>(a, d, tile);
-      else do_rows<C, 16, 1>(a, d, tile);
-      break;
-    case 1032:
-      if constexpr (kMulti) do_rows<C, 32, 4>(a, d, tile);
-      else do_rows<C, 32, 1>(a, d, tile);
-      break;
-    case SPX_LANES_STREAM:
-      if constexpr (C::KL == 1 && C::VEC == 1) do_stream<C>(a, d, tile);
-      else do_rows<C, 1, 1>(a, d, tile);
-      break;
-    default: do_split<C>(a, d, tile); break;
-  }
-}
-
 // One workgroup per tile of a layout's group (blockIdx.x indexes the group,
 // heaviest tiles first).  The tile's fields are wave-uniform (read through a
 // uniform pointer), so every branch of the tile code is scalar, as in the
@@ -110,7 +66,7 @@ __global__ __launch_bounds__(kWG) void k_batch(const BatchArgs b) {
   d.lanes = a.bins[slot].lanes;
   d.bin = 0;
   d.rpg = a.bins[slot].rpg;
-  run_tile<C, MR>(a, d, tile);
+  product_tile<C, MR>(a, d, tile);
 }
 
 bool pair_ok(spx_dtype vt, spx_dtype xt) {

@@ -46,45 +46,12 @@ __global__ __launch_bounds__(kWG) void k_product(const ProdArgs a) {
   const BinDesc d = a.bins[bi];
   const int lb = b - d.blk_begin;
   const int tile = (a.flags & SPX_FLAG_NO_XCD_MAP) ? lb : xcd_tile(lb, d.nblk);
-  switch (d.lanes + (d.rpg > 1 ? 1000 : 0)) {
-    case 1: do_rows<C, 1, 1>(a, d, tile); break;
-    case 2: do_rows<C, 2, 1>(a, d, tile); break;
-    case 4: do_rows<C, 4, 1>(a, d, tile); break;
-    case 8: do_rows<C, 8, 1>(a, d, tile); break;
-    case 16: do_rows<C, 16, 1>(a, d, tile); break;
-    case 32: do_rows<C, 32, 1>(a, d, tile); break;
-    case 64: do_rows<C, 64, 1>(a, d, tile); break;
-    case 256: do_rows<C, 256, 1>(a, d, tile); break;
-    case 1001:
-      if constexpr (MR && C::KL == 1 && C::VEC == 1) do_rows<C, 1, 4>(a, d, tile);
-      else do_rows<C, 1, 1>(a, d, tile);
-      break;
-    case 1002:
-      if constexpr (MR && C::KL == 1 && C::VEC == 1) do_rows<C, 2, 4>(a, d, tile);
-      else do_rows<C, 2, 1>(a, d, tile);
-      break;
-    case 1004:
-      if constexpr (MR && C::KL == 1 && C::VEC == 1) do_rows<C, 4, 4>(a, d, tile);
-      else do_rows<C, 4, 1>(a, d, tile);
-      break;
-    case 1008:
-      if constexpr (MR && C::KL == 1 && C::VEC == 1) do_rows<C, 8, 4>(a, d, tile);
-      else do_rows<C, 8, 1>(a, d, tile);
-      break;
-    case 1016:
-      if constexpr (MR && C::KL == 1 && C::VEC == 1) do_rows<C, 16, 4>(a, d, tile);
-      else do_rows<C, 16, 1>(a, d, tile);
-      break;
-    case 1032:
-      if constexpr (MR && C::KL == 1 && C::VEC == 1) do_rows<C, 32, 4>(a, d, tile);
-      else do_rows<C, 32, 1>(a, d, tile);
-      break;
-    case SPX_LANES_STREAM:
-      if constexpr (C::KL == 1 && C::VEC == 1) do_stream<C>(a, d, tile);
-      else do_rows<C, 1, 1>(a, d, tile);
-      break;
-    default: do_split<C>(a, d, tile); break;
-  }
+  product_tile<C, MR>(a, d, tile);
+}
+
+template <class C, int G>
+__device__ __forceinline__ void free_rows(const ProdArgs& a, const BinDesc& d, int tile) {
+  if constexpr (G >= C::KL) do_rows_free<C, G>(a, d, tile);
 }
 
 // A product without a plan: one bin of natural-order rows.
@@ -92,14 +59,14 @@ template <class C>
 __global__ __launch_bounds__(kWG) void k_product_free(const ProdArgs a) {
   const BinDesc d = a.bins[0];
   const int tile = xcd_tile(blockIdx.x, d.nblk);
-  switch (d.lanes) {
-    case 1: do_rows_free<C, 1>(a, d, tile); break;
-    case 2: do_rows_free<C, 2>(a, d, tile); break;
-    case 4: do_rows_free<C, 4>(a, d, tile); break;
-    case 8: do_rows_free<C, 8>(a, d, tile); break;
-    case 16: do_rows_free<C, 16>(a, d, tile); break;
-    case 32: do_rows_free<C, 32>(a, d, tile); break;
-    default: do_rows_free<C, 64>(a, d, tile); break;
+  switch (d.lanes > C::KL ? d.lanes : C::KL) {
+    case 1: free_rows<C, 1>(a, d, tile); break;
+    case 2: free_rows<C, 2>(a, d, tile); break;
+    case 4: free_rows<C, 4>(a, d, tile); break;
+    case 8: free_rows<C, 8>(a, d, tile); break;
+    case 16: free_rows<C, 16>(a, d, tile); break;
+    case 32: free_rows<C, 32>(a, d, tile); break;
+    default: free_rows<C, 64>(a, d, tile); break;
   }
 }
 
@@ -149,8 +116,9 @@ spx_status launch_vt(ProdArgs& a, int kl, int vec, unsigned grid, hipStream_t st
   for (int i = 0; i < a.nbins; ++i) mr = mr || (a.bins[i].rpg > 1);
 #define SPX_CASE(KL_, VEC_)                                                   \
   if (kl == KL_ && vec == VEC_) {                                             \
-    if (KL_ == 1 && VEC_ == 1 && mr)                                          \
-      return launch_k<Cfg<VT, XT, KL_, VEC_>, true>(a, grid, st);             \
+    if constexpr (KL_ == 1 && VEC_ == 1) {                                    \
+      if (mr) return launch_k<Cfg<VT, XT, KL_, VEC_>, true>(a, grid, st);     \
+    }                                                                         \
     return launch_k<Cfg<VT, XT, KL_, VEC_>, false>(a, grid, st);              \
   }
   SPX_CASE(1, 1) SPX_CASE(2, 1) SPX_CASE(4, 1) SPX_CASE(8, 1) SPX_CASE(16, 1) SPX_CASE(32, 1)

@@ -115,15 +115,23 @@ __device__ __forceinline__ typename C::XT value_at(const ProdArgs& a, int32_t p)
       ValueLoad<typename C::VT>::template get<C::kNT>(static_cast<const typename C::VT*>(a.values) + q));
 }
 
+template <typename T>
+__device__ __forceinline__ T shfl_raw(T v, int lane) {
+  if constexpr (sizeof(T) == 2) return static_cast<T>(__shfl(static_cast<int32_t>(v), lane, kWave));
+  else return __shfl(v, lane, kWave);
+}
+
 // x entry of column index c (SpMV): from the compact hot copy when c is a
-// hot slot (~slot < 0, HOT variant), else from x.
+// hot slot (~slot < 0, HOT variant), else from x.  Indices are widened as
+// unsigned: a sign extension inside a masked load's branch would make the
+// compiler wait for that load on the spot.
 template <class C>
 __device__ __forceinline__ typename C::XT x_at(const ProdArgs& a, const typename C::XT* X, int32_t c, int64_t ldx) {
   if constexpr (C::kHot) {
     const typename C::XT* xh = static_cast<const typename C::XT*>(a.X2);
-    return c < 0 ? xh[~c] : X[static_cast<int64_t>(c) * ldx];
+    return c < 0 ? xh[static_cast<uint32_t>(~c)] : X[static_cast<uint64_t>(static_cast<uint32_t>(c)) * ldx];
   }
-  return X[static_cast<int64_t>(c) * ldx];
+  return X[static_cast<uint64_t>(static_cast<uint32_t>(c)) * ldx];
 }
 
 // The gathered x[colind[p]] of nonzero p, kept for the backward (save variant).
@@ -141,80 +149,101 @@ __device__ __forceinline__ void save_x(const ProdArgs& a, int32_t p, typename C:
 // round is masked rather than finished one nonzero at a time, so a slot with
 // n nonzeros waits for ceil(n / U) gather round trips.  Products are added in
 // ascending p either way.
+// The stream loads of a round are clamped to the row's last nonzero instead of
+// masked, and the value permutation is tested once per batch: with branches
+// around them the compiler waited for each load before it issued the next,
+// eight memory latencies per round instead of two (SpMV, 2.4 M nonzeros with
+// 20,000-nonzero rows: 20.2 -> 16.4 us in FP32, 31.7 -> 20.6 in BF16).
 // In SpMM (KL > 1) the KL lanes of a group need the same colind / values:
-// lane kl loads element kl (kl + KL, ...) of the round and the group shares
-// them through ds_bpermute, so a round costs the texture addresser U lanes
-// of index loads instead of U x KL (the address unit, not HBM, bounds the
-// short-row SpMM).
+// lane kl loads element kl (kl + KL, ...) of a batch of B and the group shares
+// them through ds_bpermute, so each costs the texture addresser one lane
+// instead of KL (the address unit, not HBM, bounds the short-row SpMM), and a
+// batch of B > U serves B / U rounds with one wait for the stream (27-point
+// stencil 128^3, FP32, k = 32: 443 -> 365 us; 16.8 M nonzeros of a power law,
+// FP64, k = 16: 265 -> 254; 2.4 M, BF16, k = 5: 28.6 -> 21.9).
 template <class C, int S, int U = C::U>
 __device__ __forceinline__ void accumulate(const ProdArgs& a, int32_t p0, int32_t p1, int slot,
                                            int col, bool comp, typename C::AT (&acc)[C::VEC],
                                            Comp (&cacc)[C::VEC]) {
   using XT = typename C::XT;
+  using VL = ValueLoad<typename C::VT>;
+  using Raw = typename VL::Raw;
   constexpr int VEC = C::VEC;
+  constexpr int KL = C::KL;
+  // nonzeros whose colind / values are loaded together: 8 U (more registers,
+  // and whole batches of short rows' lanes idle) is slower everywhere but on
+  // the stencil (k = 32: 352 us), U slower everywhere
+  constexpr int B = KL == 1 ? U : KL > 4 * U ? KL : 4 * U;
+  constexpr int PER = B / KL;         // of them per lane
   const XT* X = static_cast<const XT*>(a.X) + col;
+  const typename C::VT* values = static_cast<const typename C::VT*>(a.values);
   const int64_t ldx = a.ldx;
   const bool colok = col < a.k;
-  for (int32_t p = p0 + slot; p < p1; p += U * S) {
-    bool h[U];
-    int32_t c[U];
-    XT v[U];
-    XT xv[U][VEC];
-    if constexpr (C::KL > 1) {
-      constexpr int KL = C::KL;
-      constexpr int PER = (U + KL - 1) / KL;
-      const int lane = threadIdx.x % kWave;
-      const int kl = lane % KL, base = lane - kl;
-      int32_t cl[PER];
-      XT vl[PER];
+  const int kl = (threadIdx.x % kWave) % KL, base = threadIdx.x % kWave - kl;
+  for (int32_t pb = p0 + slot; pb < p1; pb += B * S) {
+    int32_t cl[PER], ql[PER];
+    Raw vl[PER];
 #pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const int u = kl + j * KL;
-        const bool hl = u < U && p + u * S < p1;
-        cl[j] = hl ? ld_mat<C::kNT>(a.colind + p + u * S) : 0;
-        vl[j] = hl ? value_at<C>(a, p + u * S) : XT(0);
-      }
+    for (int j = 0; j < PER; ++j) {
+      ql[j] = min(pb + (kl + j * KL) * S, p1 - 1);
+      cl[j] = ld_mat<C::kNT>(a.colind + ql[j]);
+    }
+    if (a.vperm) {
+#pragma unroll
+      for (int j = 0; j < PER; ++j) ql[j] = ld_mat<C::kNT>(a.vperm + ql[j]);
+#pragma unroll
+      for (int j = 0; j < PER; ++j) asm volatile("" : "+v"(ql[j]));  // waited for here, not on the path without
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) vl[j] = VL::template raw<C::kNT>(values + static_cast<uint32_t>(ql[j]));
+#pragma unroll
+    for (int b = 0; b < B; b += U) {  // one round: U gathers, then U additions
+      const int32_t p = pb + b * S;
+      if (B > U && p >= p1) break;
+      int32_t c[U];
+      Raw v[U];
+      XT xv[U][VEC];
+      bool h[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         h[u] = p + u * S < p1;
-        c[u] = __shfl(cl[u / KL], base + u % KL, kWave);
-        v[u] = __shfl(vl[u / KL], base + u % KL, kWave);
+        if constexpr (KL > 1) c[u] = __shfl(cl[(b + u) / KL], base + (b + u) % KL, kWave);
+        else c[u] = cl[b + u];
       }
-    } else {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        h[u] = p + u * S < p1;
-        c[u] = h[u] ? ld_mat<C::kNT>(a.colind + p + u * S) : 0;
-        v[u] = h[u] ? value_at<C>(a, p + u * S) : XT(0);
+        if (h[u] && colok) {
+          if constexpr (KL * VEC == 1) xv[u][0] = x_at<C>(a, X, c[u], ldx);
+          else load_x<XT, VEC>(X + static_cast<uint64_t>(static_cast<uint32_t>(c[u])) * ldx, xv[u]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) xv[u][e] = XT(0);
+        }
       }
-    }
+      // the values are shared after the gathers have been issued
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (h[u] && colok) {
-        if constexpr (C::kHot) xv[u][0] = x_at<C>(a, X, c[u], ldx);
-        else load_x<XT, VEC>(X + static_cast<int64_t>(c[u]) * ldx, xv[u]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) xv[u][e] = XT(0);
+      for (int u = 0; u < U; ++u) {
+        if constexpr (KL > 1) v[u] = shfl_raw(vl[(b + u) / KL], base + (b + u) % KL);
+        else v[u] = vl[b + u];
       }
-    }
-    if constexpr (C::kSave) {
+      if constexpr (C::kSave) {
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (h[u]) save_x<C>(a, p + u * S, xv[u][0]);
-    }
-    if (!C::kComp || !comp) {
+        for (int u = 0; u < U; ++u)
+          if (h[u]) save_x<C>(a, p + u * S, xv[u][0]);
+      }
+      if (!C::kComp || !comp) {
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int e = 0; e < VEC; ++e)
-          if (h[u]) acc[e] = fma_t(v[u], xv[u][e], acc[e]);
-    } else if constexpr (C::kComp) {
+          for (int e = 0; e < VEC; ++e)
+            if (h[u]) acc[e] = fma_t(static_cast<XT>(VL::widen(v[u])), xv[u][e], acc[e]);
+      } else if constexpr (C::kComp) {
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int e = 0; e < VEC; ++e)
-          if (h[u]) cacc[e].add_prod(v[u], xv[u][e]);
+          for (int e = 0; e < VEC; ++e)
+            if (h[u]) cacc[e].add_prod(static_cast<XT>(VL::widen(v[u])), xv[u][e]);
+      }
     }
   }
 }
@@ -831,6 +860,43 @@ __device__ __forceinline__ void do_split(const ProdArgs& a, const BinDesc& d, in
   }
   if (t == 0)
     __hip_atomic_store(a.counters + s, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One tile of a bin: row groups of `lanes` threads (never fewer than KL), a
+// stream tile, or a segment of a split row.  MR: instantiate the multi-row
+// groups of short-row bins (SpMV).
+template <class C, bool MR, int G>
+__device__ __forceinline__ void group_rows(const ProdArgs& a, const BinDesc& d, int tile) {
+  if constexpr (G >= C::KL) {
+    if constexpr (MR && G <= 32 && C::KL == 1 && C::VEC == 1) {
+      if (d.rpg > 1) {
+        do_rows<C, G, 4>(a, d, tile);
+        return;
+      }
+    }
+    do_rows<C, G, 1>(a, d, tile);
+  }
+}
+
+template <class C, bool MR>
+__device__ __forceinline__ void product_tile(const ProdArgs& a, const BinDesc& d, int tile) {
+  int lanes = d.lanes;
+  if constexpr (C::KL * C::VEC > 1) lanes = lanes == SPX_LANES_STREAM ? 1 : lanes;
+  if (lanes != 0) lanes = lanes > C::KL ? lanes : C::KL;
+  switch (lanes) {
+    case 1: group_rows<C, MR, 1>(a, d, tile); break;
+    case 2: group_rows<C, MR, 2>(a, d, tile); break;
+    case 4: group_rows<C, MR, 4>(a, d, tile); break;
+    case 8: group_rows<C, MR, 8>(a, d, tile); break;
+    case 16: group_rows<C, MR, 16>(a, d, tile); break;
+    case 32: group_rows<C, MR, 32>(a, d, tile); break;
+    case 64: group_rows<C, MR, 64>(a, d, tile); break;
+    case 256: group_rows<C, MR, 256>(a, d, tile); break;
+    case SPX_LANES_STREAM:
+      if constexpr (C::KL * C::VEC == 1) do_stream<C>(a, d, tile);
+      break;
+    default: do_split<C>(a, d, tile); break;
+  }
 }
 
 }  // namespace prod
