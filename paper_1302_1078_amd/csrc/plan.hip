@@ -11,16 +11,23 @@
 
 #include "device.hpp"
 #include "internal.hpp"
+#include "radix.hpp"
 
 namespace spx {
 
 namespace {
 
-constexpr int kRowsPerThread = 16;
-constexpr int kBinTile = kWG * kRowsPerThread;  // 4096 rows per workgroup
+// Rows per workgroup of the partition: 64 workgroups for 131,072 rows, and one
+// launch of the scan up to 1.6 M rows of 5 bins (larger tiles leave most of the
+// chip idle on ordinary matrices: count and scatter take 7 us each there, 11
+// and 17 with 4,096 rows and three barriers per 256 of them).
+constexpr int kRowsPerThread = 8;
+constexpr int kBinTile = kWG * kRowsPerThread;
 
 constexpr int kBands = 8;  // one band of each row period per XCD
 constexpr int kMaxKeys = SPX_MAX_BINS * kBands;
+constexpr int kKeyBits = 7;
+static_assert(kMaxKeys <= 1 << kKeyBits, "partition keys in kKeyBits bits");
 
 struct BinParams {
   int32_t nbins;
@@ -50,49 +57,78 @@ __global__ __launch_bounds__(kWG) void k_bin_count(const int32_t* __restrict__ r
   if (t < kMaxKeys) cnt[t] = 0;
   __syncthreads();
   const int64_t base = static_cast<int64_t>(blockIdx.x) * kBinTile;
+  int32_t len[kRowsPerThread];
+#pragma unroll
   for (int j = 0; j < kRowsPerThread; ++j) {
     const int64_t i = base + j * kWG + t;
-    if (i < m) atomicAdd(&cnt[key_of(i, rowptr[i + 1] - rowptr[i], bp)], 1);
+    len[j] = i < m ? rowptr[i + 1] - rowptr[i] : 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kRowsPerThread; ++j) {
+    const int64_t i = base + j * kWG + t;
+    if (i < m) atomicAdd(&cnt[key_of(i, len[j], bp)], 1);
   }
   __syncthreads();
   if (t < bp.nkeys) counts[static_cast<int64_t>(t) * nblk + blockIdx.x] = cnt[t];
 }
 
-// Stable scatter: rows ranked in (round, wave, lane) order = ascending row.
+// Stable scatter of the rows and their nonzero ranges.  Wavefront w holds a
+// contiguous part of the tile, 64 rows at a time; lanes with the same key find
+// each other by ballots over its bits, and the first advances the wavefront's
+// counter (one wavefront's LDS accesses are performed in order).
 __global__ __launch_bounds__(kWG) void k_bin_scatter(const int32_t* __restrict__ rowptr, int32_t m,
                                                      const BinParams bp,
                                                      const int32_t* __restrict__ offs, int nblk,
-                                                     int32_t* __restrict__ row_perm) {
-  __shared__ int32_t run[kMaxKeys];
-  __shared__ int32_t wcnt[kWG / kWave][kMaxKeys];
+                                                     int32_t* __restrict__ row_perm, int2* __restrict__ prange) {
+  __shared__ int32_t s_cnt[kWG / kWave][kMaxKeys];
   const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
   const uint64_t lt_mask = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
-  if (t < bp.nkeys) run[t] = offs[static_cast<int64_t>(t) * nblk + blockIdx.x];
-  const int64_t base = static_cast<int64_t>(blockIdx.x) * kBinTile;
-  __syncthreads();
+  const int64_t base = static_cast<int64_t>(blockIdx.x) * kBinTile + w * (kBinTile / (kWG / kWave));
+  for (int i = t; i < kWG / kWave * kMaxKeys; i += kWG) (&s_cnt[0][0])[i] = 0;
+  int2 pr[kRowsPerThread];
+#pragma unroll
   for (int j = 0; j < kRowsPerThread; ++j) {
-    const int64_t i = base + j * kWG + t;
+    const int64_t i = base + j * kWave + lane;
+    pr[j] = i < m ? make_int2(rowptr[i], rowptr[i + 1]) : make_int2(0, 0);
+  }
+  __syncthreads();
+  int key[kRowsPerThread], rank[kRowsPerThread];
+  volatile int32_t* cnt = s_cnt[w];
+#pragma unroll
+  for (int j = 0; j < kRowsPerThread; ++j) {
+    const int64_t i = base + j * kWave + lane;
     const bool valid = i < m;
-    const int b = valid ? key_of(i, rowptr[i + 1] - rowptr[i], bp) : -1;
-    int rank = 0;
-    for (int q = 0; q < bp.nkeys; ++q) {
-      const uint64_t mask = __ballot(b == q);
-      if (b == q) rank = __popcll(mask & lt_mask);
-      if (lane == 0) wcnt[w][q] = __popcll(mask);
+    key[j] = valid ? key_of(i, pr[j].y - pr[j].x, bp) : 0;
+    uint64_t peers = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < kKeyBits; ++b) {
+      const bool bit = (key[j] >> b) & 1;
+      const uint64_t bal = __ballot(bit);
+      peers &= bit ? bal : ~bal;
     }
-    __syncthreads();
-    if (valid) {
-      int32_t pos = run[b] + rank;
-      for (int v = 0; v < w; ++v) pos += wcnt[v][b];
-      row_perm[pos] = static_cast<int32_t>(i);
+    const int r = __popcll(peers & lt_mask);
+    const int32_t old = cnt[key[j]];
+    rank[j] = old + r;
+    if (valid && r == 0) cnt[key[j]] = old + __popcll(peers);
+  }
+  __syncthreads();
+  if (t < bp.nkeys) {
+    int32_t run = offs[static_cast<int64_t>(t) * nblk + blockIdx.x];
+    for (int v = 0; v < kWG / kWave; ++v) {
+      const int32_t c = s_cnt[v][t];
+      s_cnt[v][t] = run;
+      run += c;
     }
-    __syncthreads();
-    if (t < bp.nkeys) {
-      int32_t add = 0;
-      for (int v = 0; v < kWG / kWave; ++v) add += wcnt[v][t];
-      run[t] += add;
-    }
-    __syncthreads();
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kRowsPerThread; ++j) {
+    const int64_t i = base + j * kWave + lane;
+    if (i >= m) continue;
+    const int32_t pos = s_cnt[w][key[j]] + rank[j];
+    row_perm[pos] = static_cast<int32_t>(i);
+    prange[pos] = pr[j];
   }
 }
 
@@ -120,13 +156,43 @@ __global__ void k_seg_fill(const int32_t* __restrict__ seg_first, int32_t nsplit
   for (int32_t q = seg_first[s]; q < seg_first[s + 1]; ++q) seg_row[q] = static_cast<int32_t>(s);
 }
 
-// Nonzero range of every binned row, in row_perm order (one int2 per row).
-__global__ void k_prange(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ row_perm,
-                         int32_t m, int2* __restrict__ prange) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= m) return;
-  const int32_t r = row_perm[i];
-  prange[i] = make_int2(rowptr[r], rowptr[r + 1]);
+// The end of a plan with few split rows, by one workgroup: the bin offsets,
+// and for the split rows their segments (seg_first, seg_row) and cleared
+// arrival counters.  out: bin_off[0 .. nbins], then the number of segments;
+// the host waits for them once, instead of once to size the launches of the
+// segments and once for their number.
+__global__ __launch_bounds__(kWG) void k_finish_plan(const int32_t* __restrict__ offs, int nblk, int32_t nbins,
+                                                     int32_t keys_per_bin, int32_t m, int32_t split_chunk,
+                                                     const int32_t* __restrict__ prange, int32_t* __restrict__ out,
+                                                     int32_t* __restrict__ seg_first, int32_t* __restrict__ seg_row,
+                                                     int32_t* __restrict__ counters) {
+  __shared__ int32_t wsum[radix::kWaves];
+  const int t = threadIdx.x;
+  auto first_of = [&](int b) {
+    return b == nbins ? m : (nblk > 0) ? offs[static_cast<int64_t>(b) * keys_per_bin * nblk] : 0;
+  };
+  if (t <= nbins) out[t] = first_of(t);
+  int32_t carry = 0;
+  if (split_chunk > 0) {
+    const int32_t s0 = first_of(nbins - 1), nsplit = m - s0;
+    for (int32_t base = 0; base < nsplit; base += kWG) {
+      const int32_t s = base + t;
+      int32_t segs = 0, all;
+      if (s < nsplit) {
+        const int32_t L = prange[2 * static_cast<int64_t>(s0 + s) + 1] - prange[2 * static_cast<int64_t>(s0 + s)];
+        segs = max(1, (L + split_chunk - 1) / split_chunk);
+      }
+      const int32_t f = carry + radix::block_excl_scan(segs, wsum, &all);
+      if (s < nsplit) {
+        seg_first[s] = f;
+        counters[s] = 0;
+        for (int32_t q = f; q < f + segs; ++q) seg_row[q] = s;
+      }
+      carry += all;
+    }
+    if (t == 0) seg_first[nsplit] = carry;
+  }
+  if (t == 0) out[nbins + 1] = carry;
 }
 
 __global__ void k_zero_i32(int32_t* __restrict__ p, int64_t n) {
@@ -149,6 +215,8 @@ struct PlanWs {
   double* partials;
   void* scan;
 };
+
+constexpr int64_t kFewSplit = 16384;  // 64 rounds of one workgroup
 
 bool has_split(const spx_plan_opts& o) { return o.lanes[o.nbins - 1] == 0; }
 
@@ -177,7 +245,7 @@ PlanWs carve_plan(void* ws, int32_t m, int32_t nnz, const spx_plan_opts& o, size
   w.row_perm = cv.take<int32_t>(m > 0 ? m : 1);
   w.prange = cv.take<int32_t>(2 * static_cast<int64_t>(m > 0 ? m : 1));
   w.counts = cv.take<int32_t>(nblk * o.nbins * keys_per_bin(o) + 1);
-  w.bin_off = cv.take<int32_t>(SPX_MAX_BINS + 1);
+  w.bin_off = cv.take<int32_t>(SPX_MAX_BINS + 2);  // and the segment count
   w.seg_first = cv.take<int32_t>(nsplit + 1);
   w.seg_row = cv.take<int32_t>(nseg + 1);
   w.counters = cv.take<int32_t>(nsplit + 1);
@@ -308,14 +376,22 @@ extern "C" spx_status csr_plan_create(int32_t m, int32_t n, int32_t nnz, const i
     s = exclusive_scan_i32(w.counts, w.counts, nblk * bp.nkeys, nullptr, w.scan, st);
     if (s != SPX_OK) return s;
     k_bin_scatter<<<static_cast<unsigned>(nblk), kWG, 0, st>>>(rowptr, m, bp, w.counts,
-                                                               static_cast<int>(nblk), w.row_perm);
+                                                               static_cast<int>(nblk), w.row_perm,
+                                                               reinterpret_cast<int2*>(w.prange));
     SPX_LAUNCHED("k_bin_scatter");
-    k_prange<<<grid_for(m), 256, 0, st>>>(rowptr, w.row_perm, m, reinterpret_cast<int2*>(w.prange));
-    SPX_LAUNCHED("k_prange");
   }
-  k_bin_off<<<1, 64, 0, st>>>(w.counts, static_cast<int>(nblk), opts->nbins, keys_per_bin(*opts), m,
+  // few split rows (by their bound): their segments too come from one workgroup
+  int64_t max_split, max_seg;
+  split_bounds(m, nnz, *opts, &max_split, &max_seg);
+  const bool few = max_split <= kFewSplit;
+  if (few)
+    k_finish_plan<<<1, kWG, 0, st>>>(w.counts, static_cast<int>(nblk), opts->nbins, keys_per_bin(*opts), m,
+                                     has_split(*opts) ? opts->split_chunk : 0, w.prange, w.bin_off, w.seg_first,
+                                     w.seg_row, w.counters);
+  else
+    k_bin_off<<<1, 64, 0, st>>>(w.counts, static_cast<int>(nblk), opts->nbins, keys_per_bin(*opts), m,
                               w.bin_off);
-  SPX_LAUNCHED("k_bin_off");
+  SPX_LAUNCHED("plan: bin offsets");
 
   spx_plan* p = new (std::nothrow) spx_plan();
   if (!p) return fail(SPX_ERR_INVALID, "csr_plan_create: out of host memory");
@@ -329,13 +405,15 @@ extern "C" spx_status csr_plan_create(int32_t m, int32_t n, int32_t nnz, const i
   p->seg_first = w.seg_first;
   p->counters = w.counters;
   p->partials = w.partials;
-  hipError_t e = hipMemcpyAsync(p->bin_off, w.bin_off, sizeof(int32_t) * (opts->nbins + 1),
+  int32_t host_off[SPX_MAX_BINS + 2];
+  hipError_t e = hipMemcpyAsync(host_off, w.bin_off, sizeof(int32_t) * (opts->nbins + (few ? 2 : 1)),
                                 hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     delete p;
     return hip_fail(e, "csr_plan_create: bin offsets");
   }
+  for (int b = 0; b <= opts->nbins; ++b) p->bin_off[b] = host_off[b];
   p->nsplit = 0;
   p->nseg = 0;
   p->cus = 0;
@@ -349,7 +427,9 @@ extern "C" spx_status csr_plan_create(int32_t m, int32_t n, int32_t nnz, const i
     const int nb = opts->nbins;
     const int32_t nsplit = p->bin_off[nb] - p->bin_off[nb - 1];
     p->nsplit = nsplit;
-    if (nsplit > 0) {
+    if (few) {
+      p->nseg = host_off[nb + 1];
+    } else if (nsplit > 0) {
       const int32_t* split_rows = w.row_perm + p->bin_off[nb - 1];
       k_seg_count<<<grid_for(nsplit), 256, 0, st>>>(rowptr, split_rows, nsplit, opts->split_chunk,
                                                     w.seg_first);
