@@ -24,12 +24,19 @@ def dtype_code(t: torch.Tensor) -> int:
         raise TypeError(f"unsupported dtype {t.dtype}") from None
 
 
+# Addresses go to the C entry points as plain integers (their declared argument
+# types convert them), and the current stream's handle is read without building
+# a torch.cuda.Stream: a small product is bound by this side of the call.
+
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(_device())
+
+
+_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
 
 
 def _dev(*ts):
@@ -254,7 +261,7 @@ class Plan:
 
 
 def _plan_ptr(plan):
-    return plan.handle if plan is not None else ctypes.c_void_p(0)
+    return plan.handle if plan is not None else None
 
 
 # ---------------------------------------------------------------- products
@@ -264,16 +271,19 @@ def spmv(A: CSR, x: torch.Tensor, y: torch.Tensor | None = None, plan: Plan | No
     L = _lib.load()
     _dev(A.rowptr, x)
     _contig(x)
-    if x.numel() < A.n:
-        raise ValueError(f"x has {x.numel()} entries, A has {A.n} columns")
+    m, n = A.m, A.n
+    if x.numel() < n:
+        raise ValueError(f"x has {x.numel()} entries, A has {n} columns")
     if y is None:
-        y = torch.empty(A.m, dtype=x.dtype, device=x.device)
-    _contig(y)
-    if y.numel() < A.m or y.dtype != x.dtype:
-        raise ValueError("y must hold m entries of x's dtype")
-    check(L.csr_spmv(A.m, A.n, A.nnz, _ptr(A.rowptr), _ptr(A.colind), _ptr(A.values),
-                     dtype_code(A.values), _ptr(x), _ptr(y), dtype_code(x), _plan_ptr(plan), _stream()),
-          "csr_spmv")
+        y = torch.empty(m, dtype=x.dtype, device=x.device)
+    else:
+        _contig(y)
+        if y.numel() < m or y.dtype != x.dtype:
+            raise ValueError("y must hold m entries of x's dtype")
+    status = L.csr_spmv(m, n, A.nnz, _ptr(A.rowptr), _ptr(A.colind), _ptr(A.values), dtype_code(A.values), _ptr(x),
+                        _ptr(y), dtype_code(x), _plan_ptr(plan), _stream())
+    if status:
+        check(status, "csr_spmv")
     return y
 
 
