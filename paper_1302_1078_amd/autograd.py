@@ -38,11 +38,14 @@ class GradContext:
         self.plans = plans
         self._fwd = {}
         self._csc = {}
+        # a plan waits for the device: the first has nothing queued before it, and
+        # the value map is queued after the second, so that the device is at work
+        # on it while the first product is being launched
+        self.plan = self.plan_for(k)
         self.index = transpose_index(A) if mode == 0 else None
+        self.plan_t = self.plan_t_for(k)
         self.vmap = csc_value_map(self.index) if (mode == 0 and csc_values) else None
         self.index_v = CSCIndex(self.index.colptr, self.index.rowind, None) if self.vmap is not None else None
-        self.plan = self.plan_for(k)
-        self.plan_t = self.plan_t_for(k)
 
     def plan_for(self, k: int):
         """Plan of the CSR pattern for products with k right-hand sides."""
