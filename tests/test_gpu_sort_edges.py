@@ -87,7 +87,8 @@ def test_csc_index_map_and_degree_order(spx, torch, m, n, nnz):
     assert np.array_equal(deg, np.argsort(-counts, kind="stable"))
 
 
-@pytest.mark.parametrize("nnz", [1, 255, 8191, 8192, 8193, 70_001])
+# one and two blocks, positions of up to 16, 17 and 23 bits
+@pytest.mark.parametrize("nnz", [1, 255, 8191, 8192, 8193, 65_536, 65_537, 70_001, (1 << 22) + 1])
 def test_value_map(spx, torch, nnz):
     rng = np.random.Generator(np.random.PCG64(nnz))
     perm = rng.permutation(nnz).astype(np.int32)
