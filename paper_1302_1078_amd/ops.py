@@ -33,10 +33,7 @@ def _ptr(t):
 
 
 def _stream():
-    return _raw_stream(_device())
-
-
-_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(*ts):
@@ -268,9 +265,11 @@ def _plan_ptr(plan):
 
 def spmv(A: CSR, x: torch.Tensor, y: torch.Tensor | None = None, plan: Plan | None = None) -> torch.Tensor:
     """y <- A x."""
-    L = _lib.load()
-    _dev(A.rowptr, x)
-    _contig(x)
+    rowptr, colind, values = A.rowptr, A.colind, A.values
+    if not (rowptr.is_cuda and x.is_cuda):
+        _dev(rowptr, x)
+    if not x.is_contiguous():
+        _contig(x)
     m, n = A.m, A.n
     if x.numel() < n:
         raise ValueError(f"x has {x.numel()} entries, A has {n} columns")
@@ -280,8 +279,9 @@ def spmv(A: CSR, x: torch.Tensor, y: torch.Tensor | None = None, plan: Plan | No
         _contig(y)
         if y.numel() < m or y.dtype != x.dtype:
             raise ValueError("y must hold m entries of x's dtype")
-    status = L.csr_spmv(m, n, A.nnz, _ptr(A.rowptr), _ptr(A.colind), _ptr(A.values), dtype_code(A.values), _ptr(x),
-                        _ptr(y), dtype_code(x), _plan_ptr(plan), _stream())
+    status = _lib.load().csr_spmv(m, n, colind.numel(), rowptr.data_ptr(), colind.data_ptr(), values.data_ptr(),
+                                  dtype_code(values), x.data_ptr(), y.data_ptr(), dtype_code(x),
+                                  None if plan is None else plan.handle, _stream())
     if status:
         check(status, "csr_spmv")
     return y
