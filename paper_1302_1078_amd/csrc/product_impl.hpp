@@ -161,7 +161,7 @@ __device__ __forceinline__ void save_x(const ProdArgs& a, int32_t p, typename C:
 // batch of B > U serves B / U rounds with one wait for the stream (27-point
 // stencil 128^3, FP32, k = 32: 443 -> 365 us; 16.8 M nonzeros of a power law,
 // FP64, k = 16: 265 -> 254; 2.4 M, BF16, k = 5: 28.6 -> 21.9).
-template <class C, int S, int U = C::U>
+template <class C, int S, int U = C::U, bool MASK = false>
 __device__ __forceinline__ void accumulate(const ProdArgs& a, int32_t p0, int32_t p1, int slot,
                                            int col, bool comp, typename C::AT (&acc)[C::VEC],
                                            Comp (&cacc)[C::VEC]) {
@@ -183,10 +183,17 @@ __device__ __forceinline__ void accumulate(const ProdArgs& a, int32_t p0, int32_
   for (int32_t pb = p0 + slot; pb < p1; pb += B * S) {
     int32_t cl[PER], ql[PER];
     Raw vl[PER];
+    // MASK (SpMV without a plan, rows that end in the first nonzero or two of a
+    // round): the loads past the row are left out, the loads alone, since each
+    // lane address counts (14 nonzeros a row, BF16: 48.5 us clamped, 42.8 masked);
+    // on the longer rows of a plan's groups clamping is faster (18.9 against 26.2)
+    bool in[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
+      in[j] = !MASK || pb + (kl + j * KL) * S < p1;
       ql[j] = min(pb + (kl + j * KL) * S, p1 - 1);
-      cl[j] = ld_mat<C::kNT>(a.colind + ql[j]);
+      cl[j] = 0;
+      if (in[j]) cl[j] = ld_mat<C::kNT>(a.colind + ql[j]);
     }
     if (a.vperm) {
 #pragma unroll
@@ -195,7 +202,10 @@ __device__ __forceinline__ void accumulate(const ProdArgs& a, int32_t p0, int32_
       for (int j = 0; j < PER; ++j) asm volatile("" : "+v"(ql[j]));  // waited for here, not on the path without
     }
 #pragma unroll
-    for (int j = 0; j < PER; ++j) vl[j] = VL::template raw<C::kNT>(values + static_cast<uint32_t>(ql[j]));
+    for (int j = 0; j < PER; ++j) {
+      vl[j] = Raw(0);
+      if (in[j]) vl[j] = VL::template raw<C::kNT>(values + static_cast<uint32_t>(ql[j]));
+    }
 #pragma unroll
     for (int b = 0; b < B; b += U) {  // one round: U gathers, then U additions
       const int32_t p = pb + b * S;
@@ -520,7 +530,7 @@ __device__ __forceinline__ void do_rows_free(const ProdArgs& a, const BinDesc& d
   for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
     const int col = lane_col<VEC>(a.k, c0, kl);
     clear();
-    accumulate<C, S>(a, p0, p1, slot, col, comp, acc, cacc);
+    accumulate<C, S, C::U, C::KL == 1>(a, p0, p1, slot, col, comp, acc, cacc);
     finish_small<C, GG>(a, active && !later, comp, slot, col, row, acc, cacc, nt);
   }
   __syncthreads();
