@@ -129,7 +129,10 @@ spx_status spx_plan_default_opts(int32_t k, spx_dtype vtype, spx_plan_opts *opts
  * v: f64[nnz_in].  Outputs rowptr int32[m+1], colind int32[nnz_in] and values
  * f64[nnz_in] (capacity nnz_in); *nnz_out (device int32) receives the stored
  * count, or -1 if some triplet is out of range (then the other outputs are
- * unspecified).  Requires nnz_in <= SPX_MAX_NNZ.  Workspace: csr_from_coo_workspace_bytes. */
+ * unspecified).  All nnz_in entries of `values` are written on the way.  The
+ * outputs may share memory with r, c and v (values == v then costs one more
+ * sort pass at some sizes).  Requires nnz_in <= SPX_MAX_NNZ.  Workspace:
+ * csr_from_coo_workspace_bytes. */
 spx_status csr_from_coo_workspace_bytes(int32_t m, int32_t n, int64_t nnz_in, size_t *bytes);
 spx_status csr_from_coo(int32_t m, int32_t n, int64_t nnz_in, const int32_t *r, const int32_t *c,
                         const double *v, int32_t *rowptr, int32_t *colind, double *values,
@@ -407,7 +410,8 @@ spx_status csr_rcm(int32_t m, int32_t n, int32_t nnz, const int32_t *host_rowptr
  * perm[i] of A with every column j renamed to the new index of j; the output
  * is canonical CSR (columns ascending).  Outputs rowptr_out int32[m+1],
  * colind_out int32[nnz], values_out f64[nnz]; *nnz_out (device int32)
- * receives nnz, or -1 if perm is not a permutation.  Workspace:
+ * receives nnz, or -1 if perm is not a permutation.  The outputs may be the
+ * input arrays (a permutation in place).  Workspace:
  * csr_permute_workspace_bytes.  Asynchronous on `stream`. */
 spx_status csr_permute_workspace_bytes(int32_t m, int32_t nnz, size_t *bytes);
 spx_status csr_permute(int32_t m, int32_t nnz, const int32_t *rowptr, const int32_t *colind,

@@ -322,13 +322,21 @@ extern "C" spx_status csr_from_coo(int32_t m, int32_t n, int64_t nnz_in, const i
     SPX_LAUNCHED("k_fill_i32");
     return SPX_OK;
   }
-  // the last pass lands in the workspace (the output `values` serves as the
-  // other payload buffer: k_emit reads sorted pairs while it writes)
-  const int bits = cbits + rbits, fin = (radix::passes_for(bits) & 1) ? 0 : 1;
+  // The last pass lands in the workspace, and the output `values` serves as
+  // the other payload buffer (k_emit reads sorted pairs while it writes).  An
+  // even number of passes writes `values` first in pass 0, beside other tiles'
+  // reads of the triplets; where the two share memory (a permutation in place)
+  // one more pass makes the number odd, and pass 0 then writes the workspace.
+  const int bits = cbits + rbits;
+  int passes = radix::passes_for(bits);
+  const size_t vbytes = sizeof(double) * static_cast<size_t>(nnz_in), ibytes = vbytes / 2;
+  if (overlap(values, vbytes, v, vbytes) || overlap(values, vbytes, r, ibytes) || overlap(values, vbytes, c, ibytes))
+    passes |= 1;
+  const int fin = (passes & 1) ? 0 : 1;
   radix::Pairs<uint64_t, double> buf[2];
   for (int i = 0; i < 2; ++i) buf[i] = {w.keys[i], i == fin ? w.vals : values};
   const CooSrc src{r, c, v, m, n, cbits, w.bad};
-  spx_status s = radix::sort(src, buf[0], buf[1], buf[fin], nnz_in, bits, w.radix, st);
+  spx_status s = radix::sort(src, buf[0], buf[1], buf[fin], nnz_in, bits, passes, w.radix, st);
   if (s != SPX_OK) return s;
   const unsigned tiles = static_cast<unsigned>(radix::tiles_of(nnz_in));
   k_count_heads<<<tiles, kWG, 0, st>>>(buf[fin].k, nnz_in, w.counts);
@@ -401,9 +409,10 @@ extern "C" spx_status csr_transpose_index(int32_t m, int32_t n, int32_t nnz, con
   const unsigned tiles = static_cast<unsigned>(radix::tiles_of(nnz));
   k_expand_rows<<<tiles, kWG, 0, st>>>(rowptr, m, nnz, w.rowid);
   SPX_LAUNCHED("k_expand_rows");
-  const int bits = bits_for(n > 0 ? n - 1 : 0), fin = (radix::passes_for(bits) & 1) ? 0 : 1;
+  const int bits = bits_for(n > 0 ? n - 1 : 0), passes = radix::passes_for(bits), fin = (passes & 1) ? 0 : 1;
   const radix::Pairs<uint32_t, uint64_t> a{w.keys[0], w.vals[0]}, b{w.keys[1], w.vals[1]};
-  spx_status s = radix::sort(ColSrc{colind, w.rowid}, a, b, CscSink{w.keys[fin], rowind, perm}, nnz, bits, w.radix, st);
+  spx_status s = radix::sort(ColSrc{colind, w.rowid}, a, b, CscSink{w.keys[fin], rowind, perm}, nnz, bits, passes,
+                             w.radix, st);
   if (s != SPX_OK) return s;
   k_colptr<<<grid_for(nnz), 256, 0, st>>>(w.keys[fin], n, nnz, colptr);
   SPX_LAUNCHED("k_colptr");

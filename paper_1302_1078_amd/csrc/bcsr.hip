@@ -157,8 +157,9 @@ spx_status sort_blocks(int32_t m, int32_t n, int32_t nnz, const int32_t* rowptr,
   k_block_keys<<<blocks_for(m), 256, 0, st>>>(rowptr, colind, m, a, b, cbits, w.keys, w.src, w.rowid);
   SPX_LAUNCHED("k_block_keys");
   const radix::Pairs<uint64_t, int32_t> in{w.keys, w.src}, other{w.keys2, w.src2};
-  const bool odd = radix::passes_for(cbits + rbits) & 1;
-  const spx_status s = radix::sort(in, other, in, odd ? other : in, nnz, cbits + rbits, w.radix, st);
+  const int passes = radix::passes_for(cbits + rbits);
+  const bool odd = passes & 1;
+  const spx_status s = radix::sort(in, other, in, odd ? other : in, nnz, cbits + rbits, passes, w.radix, st);
   if (s != SPX_OK) return s;
   if (odd) {
     w.keys = other.k;

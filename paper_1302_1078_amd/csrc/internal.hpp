@@ -44,6 +44,12 @@ inline spx_status check_nnz(int64_t nnz, const char* who) {
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
+// Whether two ranges of bytes share any.
+inline bool overlap(const void* p, size_t pn, const void* q, size_t qn) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+  return a < b + qn && b < a + pn;
+}
+
 // Bump allocator over a caller workspace (256-byte aligned pieces).
 struct Carve {
   char* base;

@@ -39,10 +39,9 @@ constexpr int kWaves = kWG / kWave;
 
 inline int64_t tiles_of(int64_t n) { return (n + kTile - 1) / kTile; }
 
-// Passes over `bits` key bits, and the digit width of each (never 0 passes:
-// with no bits one pass still moves the source to the sink).
+// Passes over `bits` key bits (never 0: with no bits one pass still moves the
+// source to the sink).
 inline int passes_for(int bits) { return bits <= kMaxDigit ? 1 : (bits + kMaxDigit - 1) / kMaxDigit; }
-inline int digit_bits(int bits) { return (bits + passes_for(bits) - 1) / passes_for(bits); }
 
 inline size_t count_bytes(int64_t n) {
   return align_up(sizeof(int32_t) * kMaxBins * static_cast<size_t>(tiles_of(n > 0 ? n : 1))) +
@@ -354,15 +353,17 @@ spx_status pass(const Src& src, const Dst& dst, int64_t n, int shift, int width,
   return SPX_OK;
 }
 
-// Sort n >= 1 pairs of `src` by the low `bits` key bits into `last`.  Passes
-// before the last one write `a`, then `b`, then `a` again: `last` may be the
-// pair of arrays that the final intermediate pass does not use (`a` for an
-// odd number of passes, `b` for an even one).  `b` may be the arrays `src`
-// reads, `a` may not.
+// Sort n >= 1 pairs of `src` by the low `bits` key bits into `last`, in
+// `passes` >= passes_for(bits) passes.  Passes before the last one write `a`,
+// then `b`, then `a` again: `last` may be the pair of arrays that the final
+// intermediate pass does not use (`a` for an odd number of passes, `b` for an
+// even one).  The first pass alone reads `src`, all of it while it writes: `b`
+// may be the arrays `src` reads; `a` may not, nor may `last` if there is one
+// pass.
 template <typename K, typename V, class Src, class Dst>
 spx_status sort(const Src& src, const Pairs<K, V>& a, const Pairs<K, V>& b, const Dst& last, int64_t n, int bits,
-                void* counts, hipStream_t st) {
-  const int passes = passes_for(bits), width = digit_bits(bits);
+                int passes, void* counts, hipStream_t st) {
+  const int width = (bits + passes - 1) / passes;
   spx_status s = SPX_OK;
   for (int p = 0; p < passes && s == SPX_OK; ++p) {
     const int shift = p * width;

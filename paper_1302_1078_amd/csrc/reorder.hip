@@ -457,7 +457,8 @@ extern "C" spx_status csr_degree_order(int32_t n, int32_t nnz, const int32_t* co
   // a count is at most nnz, so its complement needs no more bits than nnz
   const int bits = bits_for(nnz);
   const radix::Pairs<uint32_t, int32_t> a{w.keys[0], w.vals[0]}, b{w.keys[1], w.vals[1]};
-  return radix::sort(DegreeSrc{w.cnt, (1u << bits) - 1u}, a, b, PermSink{perm}, n, bits, w.radix, st);
+  return radix::sort(DegreeSrc{w.cnt, (1u << bits) - 1u}, a, b, PermSink{perm}, n, bits,
+                     radix::passes_for(bits), w.radix, st);
 }
 
 extern "C" spx_status csr_permute_workspace_bytes(int32_t m, int32_t nnz, size_t* bytes) {
