@@ -28,7 +28,11 @@ class GradContext:
     kept per number of right-hand sides k (a plan with split rows serves
     products up to its max_k), so a 2-D X of any width gets a plan built for
     it on first use; `k` only picks the plans built up front.  `save_gather`
-    lets a vector forward keep its gathered operand for the sampled dot."""
+    lets a vector forward keep its gathered operand for the sampled dot.
+    With plans, a context is complete when its constructor returns: nothing of
+    it is still queued on the stream that built it, and it may be used on
+    another.  With plans=False the CSC index and value map may be; another
+    stream has to wait for that one first."""
 
     def __init__(self, A: CSR, mode: int = 0, plans: bool = True, k: int = 1, csc_values: bool = True,
                  save_gather: bool = True):
@@ -38,13 +42,13 @@ class GradContext:
         self.plans = plans
         self._fwd = {}
         self._csc = {}
-        # a plan waits for the device: the first has nothing queued before it, and
-        # the value map is queued after the second, so that the device is at work
-        # on it while the first product is being launched
+        # a plan waits for the device; that of the CSC pattern comes last, so that
+        # its wait covers the index and the map as well and any stream may use
+        # the context once it is built
         self.plan = self.plan_for(k)
         self.index = transpose_index(A) if mode == 0 else None
-        self.plan_t = self.plan_t_for(k)
         self.vmap = csc_value_map(self.index) if (mode == 0 and csc_values) else None
+        self.plan_t = self.plan_t_for(k)
         self.index_v = CSCIndex(self.index.colptr, self.index.rowind, None) if self.vmap is not None else None
 
     def plan_for(self, k: int):
