@@ -210,11 +210,11 @@ struct CscSink {
 __global__ void k_colptr(const uint32_t* __restrict__ keys, int32_t n, int64_t nnz, int32_t* __restrict__ colptr) {
   const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (q >= nnz) return;
-  // column ids are assumed valid (0 <= col < n); clamp so a bad id cannot
-  // write outside colptr
-  const int32_t last = n - 1;
-  const int32_t col = static_cast<int32_t>(min(keys[q], static_cast<uint32_t>(last)));
-  const int32_t prev = (q == 0) ? -1 : static_cast<int32_t>(min(keys[q - 1], static_cast<uint32_t>(last)));
+  // column ids are assumed valid (0 <= col < n); a bad one counts as the last
+  // column (none, -1, for n = 0), so it cannot write outside colptr[0 .. n]
+  auto clamp = [n](uint32_t k) { return k < static_cast<uint32_t>(n) ? static_cast<int32_t>(k) : n - 1; };
+  const int32_t col = clamp(keys[q]);
+  const int32_t prev = (q == 0) ? -1 : clamp(keys[q - 1]);
   for (int32_t j = prev + 1; j <= col; ++j) colptr[j] = static_cast<int32_t>(q);
   if (q == nnz - 1)
     for (int32_t j = col + 1; j <= n; ++j) colptr[j] = static_cast<int32_t>(nnz);
