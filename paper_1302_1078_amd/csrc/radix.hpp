@@ -275,6 +275,19 @@ __global__ __launch_bounds__(kWG) void k_scatter(const Src src, const Dst dst, i
   }
 }
 
+// A round of a kWG-way search of rows lo < hi <= 2^31 - 1: thread t looks at
+// row search_at, and `all` of them (a prefix) being at or before the sought
+// row narrows the range.  No intermediate leaves int32 or is formed in it.
+__host__ __device__ inline int32_t search_step(int32_t lo, int32_t hi) { return (hi - lo - 1) / kWG + 1; }
+__host__ __device__ inline int64_t search_at(int32_t lo, int32_t step, int t) {
+  return static_cast<int64_t>(lo) + static_cast<int64_t>(t + 1) * step;
+}
+__host__ __device__ inline void search_narrow(int32_t& lo, int32_t& hi, int32_t step, int32_t all) {
+  lo += all * step;  // below hi: the rows counted are
+  const int64_t end = static_cast<int64_t>(lo) + step;
+  if (end < hi) hi = static_cast<int32_t>(end);
+}
+
 // Rows of the nonzeros [base, base + here) of a CSR pattern, here <= kTile:
 // row[j] belongs to position base + 1024 w + 64 j + lane (w: wavefront).  The
 // tile's first row is found by a 256-way search of rowptr, every later
@@ -286,8 +299,8 @@ __device__ __forceinline__ void tile_rows(const int32_t* __restrict__ rowptr, in
   const int t = threadIdx.x, lane = t % kWave, w = t / kWave;
   int32_t lo = 0, hi = m;  // rowptr[lo] <= base < rowptr[hi]
   while (hi - lo > 1) {
-    const int32_t step = (hi - lo + kWG - 1) / kWG;
-    const int64_t at = static_cast<int64_t>(lo) + static_cast<int64_t>(t + 1) * step;
+    const int32_t step = search_step(lo, hi);
+    const int64_t at = search_at(lo, step, t);
     const bool below = at < hi && rowptr[at] <= base;
     const int c = __popcll(__ballot(below));
     if (lane == 0) s_wsum[w] = c;
@@ -296,8 +309,7 @@ __device__ __forceinline__ void tile_rows(const int32_t* __restrict__ rowptr, in
 #pragma unroll
     for (int i = 0; i < kWaves; ++i) all += s_wsum[i];
     __syncthreads();
-    lo += all * step;
-    hi = min(hi, lo + step);
+    search_narrow(lo, hi, step, all);
   }
   for (int i = t; i < kTile; i += kWG) s_row[i] = lo;
   __syncthreads();
