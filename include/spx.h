@@ -269,7 +269,8 @@ spx_status csr_spmm(int32_t m, int32_t n, int32_t nnz, const int32_t *rowptr, co
  * CSC index of a CSR pattern (the CCS dual, Sec. 3), built on the device:
  * colptr int32[n+1]; rowind int32[nnz] and perm int32[nnz] list, column by
  * column and in ascending row order inside a column, the row and the CSR
- * position of each nonzero.  Deterministic. */
+ * position of each nonzero.  Deterministic.  rowind or perm may be written
+ * over colind. */
 spx_status csr_transpose_index_workspace_bytes(int32_t m, int32_t n, int32_t nnz, size_t *bytes);
 spx_status csr_transpose_index(int32_t m, int32_t n, int32_t nnz, const int32_t *rowptr,
                                const int32_t *colind, int32_t *colptr, int32_t *rowind,

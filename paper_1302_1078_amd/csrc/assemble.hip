@@ -409,7 +409,12 @@ extern "C" spx_status csr_transpose_index(int32_t m, int32_t n, int32_t nnz, con
   const unsigned tiles = static_cast<unsigned>(radix::tiles_of(nnz));
   k_expand_rows<<<tiles, kWG, 0, st>>>(rowptr, m, nnz, w.rowid);
   SPX_LAUNCHED("k_expand_rows");
-  const int bits = bits_for(n > 0 ? n - 1 : 0), passes = radix::passes_for(bits), fin = (passes & 1) ? 0 : 1;
+  const int bits = bits_for(n > 0 ? n - 1 : 0);
+  int passes = radix::passes_for(bits);
+  // a single pass would write rowind and perm beside other tiles' reads of colind
+  const size_t bytes = sizeof(int32_t) * static_cast<size_t>(nnz);
+  if (passes == 1 && (overlap(rowind, bytes, colind, bytes) || overlap(perm, bytes, colind, bytes))) passes = 2;
+  const int fin = (passes & 1) ? 0 : 1;
   const radix::Pairs<uint32_t, uint64_t> a{w.keys[0], w.vals[0]}, b{w.keys[1], w.vals[1]};
   spx_status s = radix::sort(ColSrc{colind, w.rowid}, a, b, CscSink{w.keys[fin], rowind, perm}, nnz, bits, passes,
                              w.radix, st);

@@ -94,3 +94,25 @@ def test_assembly_over_its_triplets(lib, torch, m, over):
     assert np.array_equal(rowptr.cpu().numpy(), ref.rowptr)
     assert np.array_equal(colind[:t].cpu().numpy(), ref.colind)
     assert np.array_equal(values[:t].cpu().numpy().view(np.uint64), ref.values.view(np.uint64))
+
+
+# 0, 3, 10 and 11 column bits: one pass (which the overlap makes two), and two
+@pytest.mark.parametrize("n", [1, 7, 1024, 1025])
+@pytest.mark.parametrize("over", ["rowind", "perm"])
+def test_csc_index_over_the_columns(lib, torch, n, over):
+    m, nnz = 50_000, 6_000_000
+    rng = np.random.Generator(np.random.PCG64(n))
+    c = rng.integers(0, n, nnz).astype(np.int32)
+    lens = rng.multinomial(nnz, np.full(m, 1.0 / m))
+    r = np.repeat(np.arange(m), lens).astype(np.int32)
+    rp, ci = dev(torch, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)), dev(torch, c)
+    colptr = torch.empty(n + 1, dtype=torch.int32, device="cuda:0")
+    other = torch.empty(nnz, dtype=torch.int32, device="cuda:0")
+    rowind, perm = (ci, other) if over == "rowind" else (other, ci)
+    ws, nb = workspace(torch, lib.csr_transpose_index_workspace_bytes, m, n, nnz)
+    assert lib.csr_transpose_index(m, n, nnz, rp.data_ptr(), ci.data_ptr(), colptr.data_ptr(), rowind.data_ptr(),
+                                   perm.data_ptr(), ws.data_ptr(), nb, stream(torch)) == 0
+    order = np.argsort(c, kind="stable")
+    assert np.array_equal(perm.cpu().numpy(), order)
+    assert np.array_equal(rowind.cpu().numpy(), r[order])
+    assert np.array_equal(colptr.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(c, minlength=n))]))
