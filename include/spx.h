@@ -301,8 +301,8 @@ spx_status csr_spmv_t(int32_t m, int32_t n, int32_t nnz, const int32_t *rowptr, 
  * uint16[nnz]) groups the nonzeros by block of SPX_CSC_BLOCK CSC positions;
  * csr_values_to_csc then streams values into `staging` (nnz elements of
  * vtype) block by block and reorders each block in LDS into values_csc.
- * Bitwise a permutation of the input.  Workspace of the map:
- * csr_csc_value_map_workspace_bytes.  Asynchronous on `stream`. */
+ * Bitwise a permutation of the input.  dest or local may be written over
+ * perm.  Workspace of the map: csr_csc_value_map_workspace_bytes.  Asynchronous on `stream`. */
 #define SPX_CSC_BLOCK 8192
 spx_status csr_csc_value_map_workspace_bytes(int32_t nnz, size_t *bytes);
 spx_status csr_csc_value_map(int32_t nnz, const int32_t *perm, int32_t *dest, uint16_t *local, void *workspace,

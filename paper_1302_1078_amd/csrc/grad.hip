@@ -613,6 +613,11 @@ __global__ __launch_bounds__(kMapThreads) void k_block_map(const int32_t* __rest
   }
 }
 
+__global__ void k_copy_i32(const int32_t* __restrict__ in, int32_t n, int32_t* __restrict__ out) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = in[i];
+}
+
 // Pass 1 tiles are XCD-contiguous (grid a multiple of 8): XCD j streams one
 // contiguous eighth of the nonzeros, so its part of every block's run is
 // contiguous and the run's lines fill in that XCD's L2 instead of being
@@ -765,7 +770,8 @@ using namespace spx;
 
 extern "C" spx_status csr_csc_value_map_workspace_bytes(int32_t nnz, size_t* bytes) {
   if (!bytes || nnz < 0) return fail(SPX_ERR_INVALID, "csr_csc_value_map_workspace_bytes: bad argument");
-  *bytes = 256;  // the map is built in LDS
+  // the map is built in LDS; a perm that shares memory with the outputs is copied first
+  *bytes = align_up(sizeof(int32_t) * static_cast<size_t>(nnz > 0 ? nnz : 1));
   return SPX_OK;
 }
 
@@ -784,6 +790,13 @@ extern "C" spx_status csr_csc_value_map(int32_t nnz, const int32_t* perm, int32_
     return fail(SPX_ERR_WORKSPACE, "csr_csc_value_map: workspace %zu < %zu bytes", ws_bytes, need);
   hipStream_t st = as_stream(stream);
   const unsigned nb = static_cast<unsigned>((static_cast<int64_t>(nnz) + SPX_CSC_BLOCK - 1) / SPX_CSC_BLOCK);
+  const size_t pbytes = sizeof(int32_t) * static_cast<size_t>(nnz);
+  if (overlap(dest, pbytes, perm, pbytes) || overlap(local, pbytes / 2, perm, pbytes)) {
+    int32_t* copy = static_cast<int32_t*>(workspace);
+    k_copy_i32<<<static_cast<unsigned>((static_cast<int64_t>(nnz) + 255) / 256), 256, 0, st>>>(perm, nnz, copy);
+    SPX_LAUNCHED("k_copy_i32");
+    perm = copy;
+  }
   k_block_map<<<nb, kMapThreads, 0, st>>>(perm, nnz, bits_for(static_cast<int64_t>(nnz) - 1), dest, local);
   SPX_LAUNCHED("k_block_map");
   return SPX_OK;

@@ -116,3 +116,20 @@ def test_csc_index_over_the_columns(lib, torch, n, over):
     assert np.array_equal(perm.cpu().numpy(), order)
     assert np.array_equal(rowind.cpu().numpy(), r[order])
     assert np.array_equal(colptr.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(c, minlength=n))]))
+
+
+@pytest.mark.parametrize("nnz", [1, 8192, 9000, 6_000_000])
+@pytest.mark.parametrize("over", ["dest", "local"])
+def test_value_map_over_perm(lib, torch, nnz, over):
+    perm = np.random.Generator(np.random.PCG64(nnz)).permutation(nnz).astype(np.int32)
+    ws, nb = workspace(torch, lib.csr_csc_value_map_workspace_bytes, nnz)
+    got = {}
+    for shared in (False, True):
+        p = dev(torch, perm)
+        dest = p if shared and over == "dest" else torch.empty(nnz, dtype=torch.int32, device="cuda:0")
+        local = p.view(torch.int16)[:nnz] if shared and over == "local" else torch.empty(
+            nnz, dtype=torch.int16, device="cuda:0")
+        assert lib.csr_csc_value_map(nnz, p.data_ptr(), dest.data_ptr(), local.data_ptr(), ws.data_ptr(), nb,
+                                     stream(torch)) == 0
+        got[shared] = dest.cpu().numpy(), local.cpu().numpy()
+    assert np.array_equal(got[True][0], got[False][0]) and np.array_equal(got[True][1], got[False][1])
