@@ -26,6 +26,7 @@ enum { kScatterT = 0, kSddmm = 1, kSddmmSaved = 2 };
 // before any use, so a lane keeps kVisit load chains in flight.  Each
 // nonzero's arithmetic is the same expression whatever the batching.
 constexpr int kVisit = 4;
+static_assert(kVisit * kWG <= kMaxLookAhead, "positions computed past the row's end");
 
 // Scatter-add merging (A^T dy with k = 1): a workgroup first adds its
 // contributions into an LDS table keyed by column (linear probing, a slot

@@ -31,9 +31,10 @@ spx_status hip_fail(hipError_t e, const char* what);
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 // nnz within the int32 position range the kernels assume: a position plus
-// one split chunk plus the widest look-ahead past a row's end (U x S <= 2,048
-// slots) stays below 2^31.
-static_assert(static_cast<int64_t>(SPX_MAX_NNZ) + SPX_MAX_SPLIT_CHUNK + 4096 <= 0x7fffffffLL,
+// one split chunk plus the widest look-ahead past a row's end (asserted where
+// a traversal steps: prod::accumulate, grad.hip) stays below 2^31.
+constexpr int kMaxLookAhead = 4096;
+static_assert(static_cast<int64_t>(SPX_MAX_NNZ) + SPX_MAX_SPLIT_CHUNK + kMaxLookAhead <= 0x7fffffffLL,
               "position headroom");
 inline spx_status check_nnz(int64_t nnz, const char* who) {
   if (nnz > SPX_MAX_NNZ)

@@ -45,8 +45,7 @@ struct Cfg {
   static constexpr bool kHot = HOT_;
   static_assert(!SAVE_ || KL_ * VEC_ == 1, "the saved gather is an SpMV (k = 1) feature");
   static_assert(!HOT_ || (KL_ * VEC_ == 1 && !SAVE_), "hot x is a plain SpMV (k = 1) feature");
-  // look-ahead past a row's end is at most U x 256 slots (SPX_MAX_NNZ headroom)
-  static_assert(U >= 1 && U * kWG <= 4096, "unroll depth");
+  static_assert(U >= 1 && U * kWG <= kMaxLookAhead, "unroll depth");
 };
 
 template <typename T, int N>
@@ -175,6 +174,7 @@ __device__ __forceinline__ void accumulate(const ProdArgs& a, int32_t p0, int32_
   // the stencil (k = 32: 352 us), U slower everywhere
   constexpr int B = KL == 1 ? U : KL > 4 * U ? KL : 4 * U;
   constexpr int PER = B / KL;         // of them per lane
+  static_assert(B * S <= kMaxLookAhead, "positions computed past the row's end");
   const XT* X = static_cast<const XT*>(a.X) + col;
   const typename C::VT* values = static_cast<const typename C::VT*>(a.values);
   const int64_t ldx = a.ldx;
