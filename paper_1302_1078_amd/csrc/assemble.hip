@@ -65,8 +65,28 @@ __global__ __launch_bounds__(kWG) void k_count_heads(const uint64_t* __restrict_
   if (threadIdx.x == 0) counts[blockIdx.x] = all;
 }
 
+// Each lane stores `value` at p[from .. to].  A lane's few entries it stores
+// itself; longer runs the wavefront stores one after the other, 64 entries at
+// a time (runs of empty rows: 5,000 triplets of 10 M rows leave 2,000 entries
+// to each head).  Called by the whole wavefront.
+__device__ __forceinline__ void wave_fill(int32_t* __restrict__ p, int64_t from, int64_t to, int32_t value) {
+  constexpr int64_t kOwn = 8;
+  uint64_t runs = __ballot(to - from >= kOwn);
+  if (to - from < kOwn)
+    for (int64_t i = from; i <= to; ++i) p[i] = value;
+  while (runs) {
+    const int l = __ffsll(static_cast<unsigned long long>(runs)) - 1;
+    runs &= runs - 1;
+    const int64_t f = __shfl(from, l, kWave), e = __shfl(to, l, kWave);
+    const int32_t v = __shfl(value, l, kWave);
+    for (int64_t i = f + static_cast<int64_t>(threadIdx.x % kWave); i <= e; i += kWave) p[i] = v;
+  }
+}
+
 // Every head emits its run.  offs: the exclusive scan of the tiles' head
 // counts; a head's place inside the tile comes from ballots, in sorted order.
+// gridDim.y workgroups share a tile, each emitting every gridDim.y-th of its
+// 64-position pieces (emit_share).
 __global__ __launch_bounds__(kWG) void k_emit(const uint64_t* __restrict__ keys, const double* __restrict__ v,
                                               const int32_t* __restrict__ offs, const int32_t* __restrict__ bad,
                                               const int32_t* __restrict__ total, int64_t nnz, int32_t m, int cbits,
@@ -76,7 +96,7 @@ __global__ __launch_bounds__(kWG) void k_emit(const uint64_t* __restrict__ keys,
   const int t = threadIdx.x, lane = t % kWave, w = t / kWave;
   const uint64_t lt_mask = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
   const int64_t base = static_cast<int64_t>(blockIdx.x) * radix::kTile + w * (radix::kTile / radix::kWaves);
-  if (blockIdx.x == 0 && t == 0) *nnz_out = (*bad) ? -1 : *total;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && t == 0) *nnz_out = (*bad) ? -1 : *total;
   // the wavefront's keys and values, all loads issued at once; the key before
   // each comes from the lane before it
   uint64_t key[radix::kItems], heads[radix::kItems];
@@ -105,14 +125,20 @@ __global__ __launch_bounds__(kWG) void k_emit(const uint64_t* __restrict__ keys,
   for (int i = 0; i < w; ++i) run += wcnt[i];
   const uint64_t cmask = (1ull << cbits) - 1ull;
   carry = first;
+  int32_t after = m, total_out = 0;  // the head of the last run: rows after it hold nothing
 #pragma unroll
   for (int j = 0; j < radix::kItems; ++j) {
     const int64_t i = base + j * kWave + lane;
     const uint64_t up = __shfl_up(key[j], 1, kWave);
     const uint64_t before = lane == 0 ? carry : up;
     carry = __shfl(key[j], kWave - 1, kWave);
+    if (j % gridDim.y != blockIdx.y) {
+      run += __popcll(heads[j]);
+      continue;
+    }
+    int32_t from = 0, to = -1, out = 0;  // rows whose offset this head sets
     if ((heads[j] >> lane) & 1) {
-      const int32_t out = run + __popcll(heads[j] & lt_mask);
+      out = run + __popcll(heads[j] & lt_mask);
       double s = val[j];
       int64_t q = i + 1;
       // a run of one, unless the next position of this wavefront's 64 is no head
@@ -125,13 +151,17 @@ __global__ __launch_bounds__(kWG) void k_emit(const uint64_t* __restrict__ keys,
       colind[out] = static_cast<int32_t>(key[j] & cmask);
       values[out] = s;
       const int32_t row = static_cast<int32_t>(key[j] >> cbits);
-      const int32_t prev = (i == 0) ? -1 : static_cast<int32_t>(before >> cbits);
-      for (int32_t rr = prev + 1; rr <= row; ++rr) rowptr[rr] = out;
-      if (q == nnz)
-        for (int32_t rr = row + 1; rr <= m; ++rr) rowptr[rr] = out + 1;
+      from = (i == 0) ? 0 : static_cast<int32_t>(before >> cbits) + 1;
+      to = row;
+      if (q == nnz) {
+        after = row;
+        total_out = out + 1;
+      }
     }
+    wave_fill(rowptr, from, to, out);
     run += __popcll(heads[j]);
   }
+  wave_fill(rowptr, static_cast<int64_t>(after) + 1, m, total_out);
 }
 
 __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t value) {
@@ -209,19 +239,27 @@ struct CscSink {
 // colptr from the column boundaries of the sorted columns.
 __global__ void k_colptr(const uint32_t* __restrict__ keys, int32_t n, int64_t nnz, int32_t* __restrict__ colptr) {
   const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (q >= nnz) return;
+  const bool in = q < nnz;
   // column ids are assumed valid (0 <= col < n); a bad one counts as the last
   // column (none, -1, for n = 0), so it cannot write outside colptr[0 .. n]
   auto clamp = [n](uint32_t k) { return k < static_cast<uint32_t>(n) ? static_cast<int32_t>(k) : n - 1; };
-  const int32_t col = clamp(keys[q]);
-  const int32_t prev = (q == 0) ? -1 : clamp(keys[q - 1]);
-  for (int32_t j = prev + 1; j <= col; ++j) colptr[j] = static_cast<int32_t>(q);
-  if (q == nnz - 1)
-    for (int32_t j = col + 1; j <= n; ++j) colptr[j] = static_cast<int32_t>(nnz);
+  const int32_t col = in ? clamp(keys[q]) : -1;
+  const int32_t prev = (in && q > 0) ? clamp(keys[q - 1]) : -1;
+  wave_fill(colptr, static_cast<int64_t>(prev) + 1, col, static_cast<int32_t>(q));
+  wave_fill(colptr, in && q == nnz - 1 ? static_cast<int64_t>(col) + 1 : static_cast<int64_t>(n) + 1, n,
+            static_cast<int32_t>(nnz));
 }
 
 inline unsigned grid_for(int64_t n, int bs = 256) {
   return static_cast<unsigned>((n + bs - 1) / bs);
+}
+
+// Workgroups per tile of the emission: enough that few triplets (5,000 are two
+// tiles) still spread over the device, which their runs of empty rows need.
+unsigned emit_share(unsigned tiles) {
+  unsigned share = 1;
+  while (share < radix::kItems && tiles * share * 2 <= 512) share *= 2;
+  return share;
 }
 
 struct CooWs {
@@ -343,7 +381,7 @@ extern "C" spx_status csr_from_coo(int32_t m, int32_t n, int64_t nnz_in, const i
   SPX_LAUNCHED("k_count_heads");
   s = exclusive_scan_i32(w.counts, w.counts, tiles, w.total, w.scan, st);
   if (s != SPX_OK) return s;
-  k_emit<<<tiles, kWG, 0, st>>>(buf[fin].k, buf[fin].v, w.counts, w.bad, w.total, nnz_in, m, cbits, rowptr, colind,
+  k_emit<<<dim3(tiles, emit_share(tiles)), kWG, 0, st>>>(buf[fin].k, buf[fin].v, w.counts, w.bad, w.total, nnz_in, m, cbits, rowptr, colind,
                                 values, nnz_out);
   SPX_LAUNCHED("k_emit");
   return SPX_OK;

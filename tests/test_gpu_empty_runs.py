@@ -73,19 +73,48 @@ def test_index_and_permutation(spx, torch, name):
     assert np.array_equal(B.rowptr.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(keys // m, minlength=m))]))
 
 
+def best_ms(torch, f):
+    times = []
+    for _ in range(8):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        torch.cuda.synchronize()
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b))
+    return min(times)
+
+
 def test_time_does_not_follow_the_empty_rows(spx, torch):
     """5,000 nonzeros: the index over 10 M rows (and one column) takes at most 10 times the index over 5,000 rows.
     Walking the rows took 400 times as long, a search 24 dependent loads more."""
     def best(m):
         A, *_ = build(spx, torch, m, 1, np.unique(np.linspace(0, m - 1, 5000).astype(np.int64)), 3)
-        times = []
-        for _ in range(8):
-            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-            torch.cuda.synchronize()
-            a.record()
-            spx.transpose_index(A)
-            b.record()
-            b.synchronize()
-            times.append(a.elapsed_time(b))
-        return min(times)
+        return best_ms(torch, lambda: spx.transpose_index(A))
     assert best(10_000_000) <= 10 * best(5_000)
+
+
+def test_assembly_time_with_many_empty_rows(spx, torch):
+    """5,000 triplets of 10 M rows: at most 10 times the assembly of 5,000 rows (rowptr is 40 MB, some 10 us of
+    stores; one lane after the other storing each head's 2,000 entries took 50 times as long)."""
+    def best(m):
+        r = torch.linspace(0, m - 1, 5000, device="cuda:0").to(torch.int32)
+        v = torch.ones(5000, dtype=torch.float64, device="cuda:0")
+        return best_ms(torch, lambda: spx.from_coo(m, m, r, r, v))
+    assert best(10_000_000) <= 10 * best(5_000)
+
+
+# runs of empty rows before the first, between and after the last triplet, each around the eight rows
+# that a lane stores by itself
+@pytest.mark.parametrize("gap", [0, 1, 7, 8, 9, 64, 65, 5000])
+def test_assembly_row_offsets(spx, torch, gap):
+    m = 3 * gap + 130 * (gap + 1) + 1
+    r = np.concatenate([[gap, gap], 2 * gap + (gap + 1) * np.arange(130), [m - 1 - gap]]).astype(np.int32)
+    c = np.arange(r.size, dtype=np.int32)[::-1].copy()
+    v = spgen.uniform(r.size, gap)
+    order = np.random.Generator(np.random.PCG64(gap)).permutation(r.size)
+    A = spx.from_coo(m, r.size, *(torch.from_numpy(a[order].copy()).to("cuda:0") for a in (r, c, v)))
+    want = np.concatenate([[0], np.cumsum(np.bincount(r, minlength=m))])
+    assert np.array_equal(A.rowptr.cpu().numpy(), want)
+    assert A.nnz == r.size
