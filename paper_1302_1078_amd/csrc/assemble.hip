@@ -65,28 +65,29 @@ __global__ __launch_bounds__(kWG) void k_count_heads(const uint64_t* __restrict_
   if (threadIdx.x == 0) counts[blockIdx.x] = all;
 }
 
-// Each lane stores `value` at p[from .. to].  A lane's few entries it stores
-// itself; longer runs the wavefront stores one after the other, 64 entries at
-// a time (runs of empty rows: 5,000 triplets of 10 M rows leave 2,000 entries
-// to each head).  Called by the whole wavefront.
-__device__ __forceinline__ void wave_fill(int32_t* __restrict__ p, int64_t from, int64_t to, int32_t value) {
-  constexpr int64_t kOwn = 8;
-  uint64_t runs = __ballot(to - from >= kOwn);
-  if (to - from < kOwn)
-    for (int64_t i = from; i <= to; ++i) p[i] = value;
+// Each lane stores `value` at the `count` entries of p that begin with `from`.
+// A lane's few entries it stores itself; longer runs the wavefront stores one
+// after the other, 64 entries at a time (runs of empty rows: 5,000 triplets of
+// 10 M rows leave 2,000 entries to each head).  Called by the whole wavefront.
+__device__ __forceinline__ void wave_fill(int32_t* __restrict__ p, uint32_t from, uint32_t count, int32_t value) {
+  constexpr uint32_t kOwn = 8;
+  uint64_t runs = __ballot(count > kOwn);
+  if (count <= kOwn)
+    for (uint32_t i = 0; i < count; ++i) p[static_cast<size_t>(from) + i] = value;
   while (runs) {
     const int l = __ffsll(static_cast<unsigned long long>(runs)) - 1;
     runs &= runs - 1;
-    const int64_t f = __shfl(from, l, kWave), e = __shfl(to, l, kWave);
+    int32_t* f = p + static_cast<uint32_t>(__shfl(static_cast<int>(from), l, kWave));
+    const uint32_t n = static_cast<uint32_t>(__shfl(static_cast<int>(count), l, kWave));
     const int32_t v = __shfl(value, l, kWave);
-    for (int64_t i = f + static_cast<int64_t>(threadIdx.x % kWave); i <= e; i += kWave) p[i] = v;
+    for (uint32_t i = threadIdx.x % kWave; i < n; i += kWave) f[i] = v;
   }
 }
 
 // Every head emits its run.  offs: the exclusive scan of the tiles' head
 // counts; a head's place inside the tile comes from ballots, in sorted order.
-// gridDim.y workgroups share a tile, each emitting every gridDim.y-th of its
-// 64-position pieces (emit_share).
+// gridDim.y (a power of two) workgroups share a tile, each emitting every
+// gridDim.y-th of its 64-position pieces (emit_share).
 __global__ __launch_bounds__(kWG) void k_emit(const uint64_t* __restrict__ keys, const double* __restrict__ v,
                                               const int32_t* __restrict__ offs, const int32_t* __restrict__ bad,
                                               const int32_t* __restrict__ total, int64_t nnz, int32_t m, int cbits,
@@ -125,18 +126,20 @@ __global__ __launch_bounds__(kWG) void k_emit(const uint64_t* __restrict__ keys,
   for (int i = 0; i < w; ++i) run += wcnt[i];
   const uint64_t cmask = (1ull << cbits) - 1ull;
   carry = first;
-  int32_t after = m, total_out = 0;  // the head of the last run: rows after it hold nothing
+  uint32_t after = static_cast<uint32_t>(m) + 1u;  // the head of the last run: rows from here hold nothing
+  int32_t total_out = 0;
 #pragma unroll
   for (int j = 0; j < radix::kItems; ++j) {
     const int64_t i = base + j * kWave + lane;
     const uint64_t up = __shfl_up(key[j], 1, kWave);
     const uint64_t before = lane == 0 ? carry : up;
     carry = __shfl(key[j], kWave - 1, kWave);
-    if (j % gridDim.y != blockIdx.y) {
+    if ((j & (gridDim.y - 1)) != blockIdx.y) {
       run += __popcll(heads[j]);
       continue;
     }
-    int32_t from = 0, to = -1, out = 0;  // rows whose offset this head sets
+    uint32_t from = 0, count = 0;  // rows whose offset this head sets
+    int32_t out = 0;
     if ((heads[j] >> lane) & 1) {
       out = run + __popcll(heads[j] & lt_mask);
       double s = val[j];
@@ -151,17 +154,17 @@ __global__ __launch_bounds__(kWG) void k_emit(const uint64_t* __restrict__ keys,
       colind[out] = static_cast<int32_t>(key[j] & cmask);
       values[out] = s;
       const int32_t row = static_cast<int32_t>(key[j] >> cbits);
-      from = (i == 0) ? 0 : static_cast<int32_t>(before >> cbits) + 1;
-      to = row;
+      from = (i == 0) ? 0u : static_cast<uint32_t>(before >> cbits) + 1u;
+      count = static_cast<uint32_t>(row) + 1u - from;
       if (q == nnz) {
-        after = row;
+        after = static_cast<uint32_t>(row) + 1u;
         total_out = out + 1;
       }
     }
-    wave_fill(rowptr, from, to, out);
+    wave_fill(rowptr, from, count, out);
     run += __popcll(heads[j]);
   }
-  wave_fill(rowptr, static_cast<int64_t>(after) + 1, m, total_out);
+  wave_fill(rowptr, after, static_cast<uint32_t>(m) + 1u - after, total_out);
 }
 
 __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t value) {
@@ -243,11 +246,13 @@ __global__ void k_colptr(const uint32_t* __restrict__ keys, int32_t n, int64_t n
   // column ids are assumed valid (0 <= col < n); a bad one counts as the last
   // column (none, -1, for n = 0), so it cannot write outside colptr[0 .. n]
   auto clamp = [n](uint32_t k) { return k < static_cast<uint32_t>(n) ? static_cast<int32_t>(k) : n - 1; };
-  const int32_t col = in ? clamp(keys[q]) : -1;
   const int32_t prev = (in && q > 0) ? clamp(keys[q - 1]) : -1;
-  wave_fill(colptr, static_cast<int64_t>(prev) + 1, col, static_cast<int32_t>(q));
-  wave_fill(colptr, in && q == nnz - 1 ? static_cast<int64_t>(col) + 1 : static_cast<int64_t>(n) + 1, n,
-            static_cast<int32_t>(nnz));
+  const int32_t col = in ? clamp(keys[q]) : prev;
+  wave_fill(colptr, static_cast<uint32_t>(prev + 1), col > prev ? static_cast<uint32_t>(col - prev) : 0u,
+            static_cast<int32_t>(q));
+  if (blockIdx.x + 1 == gridDim.x)
+    wave_fill(colptr, static_cast<uint32_t>(col + 1), q == nnz - 1 ? static_cast<uint32_t>(n - col) : 0u,
+              static_cast<int32_t>(nnz));
 }
 
 inline unsigned grid_for(int64_t n, int bs = 256) {
