@@ -66,6 +66,9 @@ __device__ __forceinline__ int lane_col(int32_t k, int c0, int kl) {
   else return col;
 }
 
+// N consecutive elements of a row of X in global memory, at any element-aligned
+// address.  Not for LDS: a 16-byte LDS read needs a 16-byte aligned address, so
+// without that promise it becomes four (load_group makes it).
 template <typename T, int N>
 __device__ __forceinline__ void load_x(const T* p, T (&out)[N]) {
   if constexpr (N == 1) {

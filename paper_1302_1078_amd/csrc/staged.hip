@@ -264,7 +264,7 @@ __device__ __forceinline__ void accumulate_lds(const ProdArgs& a, const typename
 #pragma unroll
     for (int uu = 0; uu < U; ++uu) {
       if (h[uu] && colok) {
-        load_x<XT, VEC>(Xb + c[uu] * a.k, xv[uu]);
+        load_group<false>(Xb + c[uu] * a.k, xv[uu]);  // k is a multiple of VEC: aligned
       } else {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) xv[uu][e] = XT(0);
@@ -497,7 +497,7 @@ __device__ __forceinline__ void accumulate_pipe(const ProdArgs& a, const unsigne
 #pragma unroll
     for (int uu = 0; uu < U; ++uu) {
       if (h[uu] && colok) {
-        load_x<XT, VEC>(Xb + c[uu] * a.k, xv[uu]);
+        load_group<false>(Xb + c[uu] * a.k, xv[uu]);  // k is a multiple of VEC: aligned
       } else {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) xv[uu][e] = XT(0);
