@@ -62,18 +62,21 @@ struct HotWs {
   size_t deg_bytes;
 };
 
+// The plan keeps this workspace for its life, so the degree order's own
+// workspace, needed before anything but perm is written, lies over the rest.
 HotWs carve_hot(void* ws, int32_t n, int32_t nnz, int32_t hot, size_t* bytes) {
   Carve cv(ws, ~size_t(0));
   HotWs w;
+  w.perm = cv.take<int32_t>(n > 0 ? n : 1);
+  Carve over = cv;
   w.colind_hot = cv.take<int32_t>(nnz > 0 ? nnz : 1);
   w.hot_cols = cv.take<int32_t>(hot > 0 ? hot : 1);
   w.x_hot = cv.take<double>(hot > 0 ? hot : 1);
-  w.perm = cv.take<int32_t>(n > 0 ? n : 1);
   w.slot = cv.take<int32_t>(n > 0 ? n : 1);
   w.deg_bytes = 0;
   csr_degree_order_workspace_bytes(n, nnz, &w.deg_bytes);
-  w.deg = cv.take<char>(w.deg_bytes);
-  *bytes = cv.used;
+  w.deg = over.take<char>(w.deg_bytes);
+  *bytes = cv.used > over.used ? cv.used : over.used;
   return w;
 }
 

@@ -310,6 +310,10 @@ __global__ void k_col_count(const int32_t* __restrict__ colind, int64_t nnz, int
 // of them (4.8 M nonzeros: 289 us with an atomic each, 62 us with the pass).
 constexpr int kCountWindow = 4096;       // columns counted in LDS, from the tile's first group on
 constexpr int64_t kGroupedCount = 1 << 17;  // nonzeros from which the pass over the columns pays for itself
+// Nonzeros grouped at a time: bounds the workspace (5 bytes each) to 168 MB.
+// Pieces of 2^23 would bound it to 42 MB, but take 268 us instead of 227 for
+// 16.8 M nonzeros, a scan and the ends of three launches more.
+constexpr int64_t kGroupedPiece = 1 << 25;
 
 struct ColKeySrc {
   const int32_t* colind;
@@ -381,6 +385,12 @@ struct DegreeWs {
   void* radix;
 };
 
+// Nonzeros of each piece: equal pieces, whole tiles.
+int64_t grouped_piece(int64_t nnz) {
+  const int64_t pieces = (nnz + kGroupedPiece - 1) / kGroupedPiece;
+  return pieces < 2 ? nnz : radix::tiles_of((nnz + pieces - 1) / pieces) * radix::kTile;
+}
+
 DegreeWs carve_degree(void* ws, int32_t n, int32_t nnz, size_t* bytes) {
   Carve cv(ws, ~size_t(0));
   const int64_t e = n > 0 ? n : 1;
@@ -390,8 +400,9 @@ DegreeWs carve_degree(void* ws, int32_t n, int32_t nnz, size_t* bytes) {
     w.keys[i] = cv.take<uint32_t>(e);
     w.vals[i] = cv.take<int32_t>(e);
   }
-  w.grouped = cv.take<uint32_t>(nnz >= kGroupedCount ? nnz : 1);
-  w.radix = cv.take<char>(radix::count_bytes(nnz > n ? nnz : n));
+  const int64_t piece = nnz >= kGroupedCount ? grouped_piece(nnz) : 1;
+  w.grouped = cv.take<uint32_t>(piece);
+  w.radix = cv.take<char>(radix::count_bytes(piece > n ? piece : n));
   *bytes = cv.used;
   return w;
 }
@@ -445,11 +456,15 @@ extern "C" spx_status csr_degree_order(int32_t n, int32_t nnz, const int32_t* co
   if (nnz >= kGroupedCount) {
     const int bits = bits_for(n - 1);
     const int width = bits < radix::kMaxDigit ? bits : radix::kMaxDigit, shift = bits - width;
-    s = radix::pass(ColKeySrc{colind}, KeySink{w.grouped}, nnz, shift, width, w.radix, st);
-    if (s != SPX_OK) return s;
-    k_col_count_grouped<<<static_cast<unsigned>(radix::tiles_of(nnz)), kWG, 0, st>>>(
-        w.grouped, nnz, n, shift, (1u << width) - 1u, w.cnt);
-    SPX_LAUNCHED("k_col_count_grouped");
+    const int64_t piece = grouped_piece(nnz);
+    for (int64_t p = 0; p < nnz; p += piece) {
+      const int64_t here = nnz - p < piece ? nnz - p : piece;
+      s = radix::pass(ColKeySrc{colind + p}, KeySink{w.grouped}, here, shift, width, w.radix, st);
+      if (s != SPX_OK) return s;
+      k_col_count_grouped<<<static_cast<unsigned>(radix::tiles_of(here)), kWG, 0, st>>>(
+          w.grouped, here, n, shift, (1u << width) - 1u, w.cnt);
+      SPX_LAUNCHED("k_col_count_grouped");
+    }
   } else if (nnz > 0) {
     k_col_count<<<blocks_for(nnz), 256, 0, st>>>(colind, nnz, n, w.cnt);
     SPX_LAUNCHED("k_col_count");
