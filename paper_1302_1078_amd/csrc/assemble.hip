@@ -300,15 +300,17 @@ struct CscWs {
   void* radix;
 };
 
-CscWs carve_csc(void* ws, int64_t nnz, size_t* bytes) {
+// Passes before the last write keys[0] / vals[0] and, from three passes on,
+// keys[1] / vals[1]; the last one leaves its keys in the pair it does not read.
+CscWs carve_csc(void* ws, int32_t n, int64_t nnz, size_t* bytes) {
   Carve cv(ws, ~size_t(0));
   const int64_t e = nnz > 0 ? nnz : 1;
   CscWs w;
   w.rowid = cv.take<int32_t>(e);
-  for (int i = 0; i < 2; ++i) {
-    w.keys[i] = cv.take<uint32_t>(e);
-    w.vals[i] = cv.take<uint64_t>(e);
-  }
+  w.keys[0] = cv.take<uint32_t>(e);
+  w.keys[1] = cv.take<uint32_t>(e);
+  w.vals[0] = cv.take<uint64_t>(e);
+  w.vals[1] = cv.take<uint64_t>(radix::passes_for(bits_for(n > 0 ? n - 1 : 0)) > 2 ? e : 1);
   w.radix = cv.take<char>(radix::count_bytes(e));
   *bytes = cv.used;
   return w;
@@ -412,9 +414,9 @@ extern "C" spx_status csr_validate(int32_t m, int32_t n, int32_t nnz, const int3
 }
 
 namespace {
-size_t transpose_ws(int64_t nnz) {
+size_t transpose_ws(int32_t n, int64_t nnz) {
   size_t bytes;
-  carve_csc(nullptr, nnz, &bytes);
+  carve_csc(nullptr, n, nnz, &bytes);
   return bytes;
 }
 }  // namespace
@@ -423,7 +425,7 @@ extern "C" spx_status csr_transpose_index_workspace_bytes(int32_t m, int32_t n, 
                                                           size_t* bytes) {
   if (!bytes || m < 0 || n < 0 || nnz < 0)
     return fail(SPX_ERR_INVALID, "csr_transpose_index_workspace_bytes: bad arguments");
-  *bytes = transpose_ws(nnz);
+  *bytes = transpose_ws(n, nnz);
   return SPX_OK;
 }
 
@@ -438,9 +440,9 @@ extern "C" spx_status csr_transpose_index(int32_t m, int32_t n, int32_t nnz, con
   }
   if (!colptr || (nnz > 0 && (!rowptr || !colind || !rowind || !perm)))
     return fail(SPX_ERR_INVALID, "csr_transpose_index: null pointer");
-  if (!workspace || ws_bytes < transpose_ws(nnz))
+  if (!workspace || ws_bytes < transpose_ws(n, nnz))
     return fail(SPX_ERR_WORKSPACE, "csr_transpose_index: workspace %zu < %zu bytes", ws_bytes,
-                transpose_ws(nnz));
+                transpose_ws(n, nnz));
   hipStream_t st = as_stream(stream);
   if (nnz == 0) {
     k_fill_i32<<<grid_for(int64_t(n) + 1), 256, 0, st>>>(colptr, int64_t(n) + 1, 0);
@@ -448,7 +450,7 @@ extern "C" spx_status csr_transpose_index(int32_t m, int32_t n, int32_t nnz, con
     return SPX_OK;
   }
   size_t need;
-  const CscWs w = carve_csc(workspace, nnz, &need);
+  const CscWs w = carve_csc(workspace, n, nnz, &need);
   const unsigned tiles = static_cast<unsigned>(radix::tiles_of(nnz));
   k_expand_rows<<<tiles, kWG, 0, st>>>(rowptr, m, nnz, w.rowid);
   SPX_LAUNCHED("k_expand_rows");

@@ -96,8 +96,8 @@ def test_assembly_over_its_triplets(lib, torch, m, over):
     assert np.array_equal(values[:t].cpu().numpy().view(np.uint64), ref.values.view(np.uint64))
 
 
-# 0, 3, 10 and 11 column bits: one pass (which the overlap makes two), and two
-@pytest.mark.parametrize("n", [1, 7, 1024, 1025])
+# 0, 3, 10 and 11 column bits: one pass (which the overlap makes two), and two; 21: three
+@pytest.mark.parametrize("n", [1, 7, 1024, 1025, (1 << 20) + 1])
 @pytest.mark.parametrize("over", ["rowind", "perm"])
 def test_csc_index_over_the_columns(lib, torch, n, over):
     m, nnz = 50_000, 6_000_000

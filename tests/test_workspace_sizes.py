@@ -34,3 +34,10 @@ def test_degree_order_does_not_grow_with_the_nonzeros(lib):
     n = 1 << 20
     sizes = [query(lib.csr_degree_order_workspace_bytes, n, nnz) for nnz in (50_000_000, 300_000_000, 2_000_000_000)]
     assert max(sizes) <= 21 * n + (5 << 25) + SLACK
+
+
+@pytest.mark.parametrize("n,per", [(7, 21), (1 << 20, 21), ((1 << 20) + 1, 29), ((1 << 31) - 1, 29)])
+def test_csc_index(lib, n, per):
+    """Row, two key arrays and a 64-bit payload, and a second payload above two sort passes (20 column bits)."""
+    nnz = 10_000_000
+    assert query(lib.csr_transpose_index_workspace_bytes, 1000, n, nnz) <= per * nnz + SLACK
