@@ -174,8 +174,12 @@ __device__ __forceinline__ void accumulate(const ProdArgs& a, int32_t p0, int32_
   constexpr int KL = C::KL;
   // nonzeros whose colind / values are loaded together: 8 U (more registers,
   // and whole batches of short rows' lanes idle) is slower everywhere but on
-  // the stencil (k = 32: 352 us), U slower everywhere
-  constexpr int B = KL == 1 ? U : KL > 4 * U ? KL : 4 * U;
+  // the stencil (k = 32: 352 us), U slower everywhere.  With two lanes a batch
+  // of 4 U is eight loads a lane, which only rows of whole workgroups fill (8
+  // nonzeros a row, k = 2, FP32: 13.3 us, 2 U 11.1; 60 a row 68.5, 63.7; a
+  // power law's long rows the other way, k = 5: 24.8 us with 2 U everywhere,
+  // 23.0 so)
+  constexpr int B = KL == 1 ? U : KL == 2 && S <= 32 ? 2 * U : KL > 4 * U ? KL : 4 * U;
   constexpr int PER = B / KL;         // of them per lane
   static_assert(B * S <= kMaxLookAhead, "positions computed past the row's end");
   const XT* X = static_cast<const XT*>(a.X) + col;
