@@ -51,7 +51,8 @@ __global__ __launch_bounds__(kWG) void k_product(const ProdArgs a) {
 
 template <class C, int G>
 __device__ __forceinline__ void free_rows(const ProdArgs& a, const BinDesc& d, int tile) {
-  if constexpr (G >= C::KL) do_rows_free<C, G>(a, d, tile);
+  if constexpr (C::KL * C::VEC == 1) spmv_rows_free<C, G>(a, d, tile);
+  else if constexpr (G >= C::KL) spmm_rows_free<C, G>(a, d, tile);
 }
 
 // A product without a plan: one bin of natural-order rows.

@@ -190,7 +190,7 @@ __device__ __forceinline__ void accumulate(const ProdArgs& a, int32_t p0, int32_
   for (int32_t pb = p0 + slot; pb < p1; pb += B * S) {
     int32_t cl[PER], ql[PER];
     Raw vl[PER];
-    // MASK (SpMV without a plan, rows that end in the first nonzero or two of a
+    // MASK (no plan and KL = 1: rows that end in the first nonzero or two of a
     // round): the loads past the row are left out, the loads alone, since each
     // lane address counts (14 nonzeros a row, BF16: 48.5 us clamped, 42.8 masked);
     // on the longer rows of a plan's groups clamping is faster (18.9 against 26.2)
@@ -500,57 +500,122 @@ constexpr int free_unroll() {
   return C::VEC == 1 ? 8 : 4;
 }
 
-template <class C, int G>
-__device__ __forceinline__ void do_rows_free(const ProdArgs& a, const BinDesc& d, int tile) {
+template <class C>
+__device__ __forceinline__ void clear_sums(typename C::AT (&acc)[C::VEC], Comp (&cacc)[C::VEC]) {
+#pragma unroll
+  for (int e = 0; e < C::VEC; ++e) {
+    acc[e] = 0;
+    cacc[e].init();
+  }
+}
+
+// A long row by the whole workgroup.
+template <class C>
+__device__ __forceinline__ void do_long_row(const ProdArgs& a, int32_t row, int32_t p0, int32_t p1, bool nt) {
   constexpr int KL = C::KL, VEC = C::VEC;
-  constexpr int S = (G >= KL) ? G / KL : 1;
-  constexpr int GG = S * KL;
-  constexpr int NG = kWG / GG;
-  static_assert(GG <= kWave, "groups inside one wavefront");
+  const int t = threadIdx.x;
+  const bool comp = C::kComp && (p1 - p0 > a.kahan_len);
+  typename C::AT acc[VEC];
+  Comp cacc[VEC];
+  for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
+    const int col = lane_col<VEC>(a.k, c0, t % KL);
+    clear_sums<C>(acc, cacc);
+    accumulate<C, kWG / KL, free_unroll<C>()>(a, p0, p1, t / KL, col, comp, acc, cacc);
+    finish_workgroup<C>(a, comp, col, row, acc, cacc, nt);
+  }
+}
+
+// SpMV.  The groups' ranges are on their way while the workgroup clears its
+// list: with the loads behind that barrier, or the long rows counted in front
+// of one, short rows wait for it (24 nonzeros a row, BF16: 48.0 and 52.4 us,
+// so 47.0; without a list 46.9).
+template <class C, int G>
+__device__ __forceinline__ void spmv_rows_free(const ProdArgs& a, const BinDesc& d, int tile) {
+  constexpr int NG = kWG / G;
+  static_assert(C::KL * C::VEC == 1 && G <= kWave, "groups inside one wavefront");
   __shared__ int32_t s_long[NG];
   __shared__ int32_t s_nlong;
   if (tile * NG >= d.nrows) return;  // whole workgroup idle (uniform)
-  const int t = threadIdx.x;
-  const int ln = t % GG, slot = ln / KL, kl = ln % KL;
+  const int t = threadIdx.x, slot = t % G;
   const bool nt = !(a.flags & SPX_FLAG_NO_NT_STORE);
   if (t == 0) s_nlong = 0;
-  __syncthreads();
-  const int idx = tile * NG + t / GG;
+  const int idx = tile * NG + t / G;
   const bool active = idx < d.nrows;
   int32_t row = 0, p0 = 0, p1 = 0;
   if (active) row_range(a, d, idx, row, p0, p1);
-  const bool later = p1 - p0 > kFreeRounds * C::U * S;
+  __syncthreads();
+  const bool later = p1 - p0 > kFreeRounds * C::U * G;
   if (later) {
-    if (ln == 0) s_long[atomicAdd(&s_nlong, 1)] = row;
+    if (slot == 0) s_long[atomicAdd(&s_nlong, 1)] = row;
     p1 = p0;
   }
-  typename C::AT acc[VEC];
-  Comp cacc[VEC];
-  auto clear = [&]() {
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      acc[e] = 0;
-      cacc[e].init();
-    }
-  };
   const bool comp = C::kComp && (p1 - p0 > a.kahan_len);
-  for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
-    const int col = lane_col<VEC>(a.k, c0, kl);
-    clear();
-    accumulate<C, S, C::U, C::KL == 1>(a, p0, p1, slot, col, comp, acc, cacc);
-    finish_small<C, GG>(a, active && !later, comp, slot, col, row, acc, cacc, nt);
-  }
+  typename C::AT acc[1];
+  Comp cacc[1];
+  clear_sums<C>(acc, cacc);
+  accumulate<C, G, C::U, true>(a, p0, p1, slot, 0, comp, acc, cacc);
+  finish_small<C, G>(a, active && !later, comp, slot, 0, row, acc, cacc, nt);
   __syncthreads();
   const int32_t n = __builtin_amdgcn_readfirstlane(s_nlong);
   for (int32_t i = 0; i < n; ++i) {
     const int32_t r = __builtin_amdgcn_readfirstlane(s_long[i]);
-    const int32_t q0 = a.rowptr[r], q1 = a.rowptr[r + 1];
-    const bool lcomp = C::kComp && (q1 - q0 > a.kahan_len);
-    for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
-      const int col = lane_col<VEC>(a.k, c0, t % KL);
-      clear();
-      accumulate<C, kWG / KL, free_unroll<C>()>(a, q0, q1, t / KL, col, lcomp, acc, cacc);
-      finish_workgroup<C>(a, lcomp, col, r, acc, cacc, nt);
+    do_long_row<C>(a, r, a.rowptr[r], a.rowptr[r + 1], nt);
+  }
+}
+
+// SpMM.  A row that the workgroup serves costs it about three rounds besides
+// the row's loads, while the groups walk theirs side by side: with n rows above
+// kFreeRounds rounds in a workgroup, those above 4 n rounds are left to it, and
+// none where more than half its groups have one.  (k = 8, FP32, a fifth of the
+// rows with 67 nonzeros and one in the others: 96 us with every row above 8
+// rounds left to the workgroup, 43 so, 42 with none; a power law of 16.8 M
+// nonzeros, k = 5, BF16: 295, 300 and 2,520 us.)  The rows are counted before
+// they are walked: one barrier, where the wavefronts arrive together.
+template <class C, int G>
+__device__ __forceinline__ void spmm_rows_free(const ProdArgs& a, const BinDesc& d, int tile) {
+  constexpr int KL = C::KL, VEC = C::VEC;
+  constexpr int S = G / KL;
+  constexpr int NG = kWG / G;
+  static_assert(KL * VEC > 1 && G >= KL && G <= kWave, "groups inside one wavefront");
+  __shared__ int32_t s_long[kWG / kWave][kWave / G];
+  __shared__ int32_t s_nlong[kWG / kWave];
+  if (tile * NG >= d.nrows) return;  // whole workgroup idle (uniform)
+  const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
+  const int ln = t % G, slot = ln / KL, kl = ln % KL;
+  const bool nt = !(a.flags & SPX_FLAG_NO_NT_STORE);
+  const int idx = tile * NG + t / G;
+  const bool active = idx < d.nrows;
+  int32_t row = 0, p0 = 0, p1 = 0;
+  if (active) row_range(a, d, idx, row, p0, p1);
+  const bool is_long = ln == 0 && p1 - p0 > kFreeRounds * C::U * S;
+  const uint64_t longs = __ballot(is_long);
+  if (is_long) s_long[w][__popcll(longs & ((1ull << lane) - 1ull))] = row;
+  if (lane == 0) s_nlong[w] = __popcll(longs);
+  __syncthreads();
+  int32_t nlong = 0;
+#pragma unroll
+  for (int v = 0; v < kWG / kWave; ++v) nlong += s_nlong[v];
+  nlong = __builtin_amdgcn_readfirstlane(nlong);
+  const bool groups_only = nlong == 0 || 2 * nlong > NG;
+  const int32_t limit = C::U * S * max(kFreeRounds, 4 * nlong);
+  const bool later = !groups_only && p1 - p0 > limit;
+  if (later) p1 = p0;
+  const bool comp = C::kComp && (p1 - p0 > a.kahan_len);
+  typename C::AT acc[VEC];
+  Comp cacc[VEC];
+  for (int c0 = 0; c0 < a.k; c0 += KL * VEC) {
+    const int col = lane_col<VEC>(a.k, c0, kl);
+    clear_sums<C>(acc, cacc);
+    accumulate<C, S, C::U, KL == 1>(a, p0, p1, slot, col, comp, acc, cacc);
+    finish_small<C, G>(a, active && !later, comp, slot, col, row, acc, cacc, nt);
+  }
+  if (groups_only) return;
+  for (int v = 0; v < kWG / kWave; ++v) {
+    const int32_t n = __builtin_amdgcn_readfirstlane(s_nlong[v]);
+    for (int32_t i = 0; i < n; ++i) {
+      const int32_t r = __builtin_amdgcn_readfirstlane(s_long[v][i]);
+      const int32_t q0 = a.rowptr[r], q1 = a.rowptr[r + 1];
+      if (q1 - q0 > limit) do_long_row<C>(a, r, q0, q1, nt);  // else its group served it
     }
   }
 }
