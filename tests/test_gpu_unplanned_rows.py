@@ -34,7 +34,7 @@ def matrix(per_block, other, seed):
     return oracle.CSR(m, n, rowptr, cols, values)
 
 
-@pytest.mark.parametrize("per_block", [0, 1, 2, 5, 16, 32, 33, 64])
+@pytest.mark.parametrize("per_block", [0, 1, 2, 3, 8, 16, 32, 33, 64])
 @pytest.mark.parametrize("other", [1, 12])
 @pytest.mark.parametrize("vname,k", [("f64", 1), ("f64", 3), ("f64", 16), ("f32", 1), ("f32", 2), ("f32", 8),
                                      ("bf16", 1), ("bf16", 32)])
