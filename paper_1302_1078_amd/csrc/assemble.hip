@@ -17,15 +17,6 @@ namespace spx {
 
 namespace {
 
-inline int bits_for(int64_t x) {  // bits needed to represent x >= 0
-  int b = 0;
-  while (x > 0) {
-    ++b;
-    x >>= 1;
-  }
-  return b;
-}
-
 // Triplets as the source of the first sort pass.  A triplet out of range sets
 // *bad and sorts as (0, 0).
 struct CooSrc {

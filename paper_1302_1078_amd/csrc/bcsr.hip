@@ -25,15 +25,6 @@
 namespace spx {
 namespace {
 
-inline int bits_for(int64_t x) {
-  int b = 0;
-  while (x > 0) {
-    ++b;
-    x >>= 1;
-  }
-  return b;
-}
-
 inline unsigned blocks_for(int64_t n) { return static_cast<unsigned>((n + 255) / 256); }
 
 bool shape_ok(int a, int b) {

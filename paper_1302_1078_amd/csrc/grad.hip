@@ -758,12 +758,6 @@ __global__ __launch_bounds__(kWG) void k_from_staging(const T* __restrict__ stag
   for (int32_t i = threadIdx.x; i < cnt; i += kWG) __builtin_nontemporal_store(blk[i], out + b0 + i);
 }
 
-int bits_for(int64_t v) {
-  int b = 1;
-  while ((int64_t(1) << b) <= v) ++b;
-  return b;
-}
-
 }  // namespace
 }  // namespace spx
 

@@ -45,6 +45,16 @@ inline spx_status check_nnz(int64_t nnz, const char* who) {
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
+// Bits needed to represent x >= 0.
+inline int bits_for(int64_t x) {
+  int b = 0;
+  while (x > 0) {
+    ++b;
+    x >>= 1;
+  }
+  return b;
+}
+
 // Whether two ranges of bytes share any.
 inline bool overlap(const void* p, size_t pn, const void* q, size_t qn) {
   const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);

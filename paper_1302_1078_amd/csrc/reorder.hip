@@ -368,15 +368,6 @@ struct PermSink {
   __device__ __forceinline__ void put_val(int64_t i, int32_t x) const { perm[i] = x; }
 };
 
-int bits_for(int64_t x) {  // bits needed to represent x >= 0
-  int b = 0;
-  while (x > 0) {
-    ++b;
-    x >>= 1;
-  }
-  return b;
-}
-
 struct DegreeWs {
   int32_t* cnt;
   uint32_t* keys[2];
