@@ -161,8 +161,8 @@ struct spx_plan {
   int32_t* tile_off;                  // device, [ntiles + 1]: offset of the tile's column list
   int32_t* tcols;                     // device: the tiles' sorted distinct columns, concatenated
   uint16_t* loc;                      // device, [nnz]: window index of each nonzero of a staged tile
-  // hot x (csr_plan_attach_hot_x; hot == 0: none): SpMV keeps the x entries
-  // of the hot most-used columns in LDS
+  // hot x (csr_plan_attach_hot_x; hot == 0: none): SpMV packs the x entries of
+  // the hot most-used columns together, per call
   int32_t hot;                        // number of hot columns
   int32_t hot_xtype;                  // spx_dtype of the x it serves
   const int32_t* hot_cols;            // device, [hot]: the hot columns, most used first

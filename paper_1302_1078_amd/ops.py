@@ -211,8 +211,8 @@ class Plan:
         return self
 
     def attach_hot_x(self, A: CSR, hot: int, xdtype=torch.float64) -> "Plan":
-        """Keep the x entries of the `hot` most-used columns in LDS for SpMV
-        through this plan (csr_plan_attach_hot_x).  Returns self."""
+        """Pack the x entries of the `hot` most-used columns together, per call,
+        for SpMV through this plan (csr_plan_attach_hot_x).  Returns self."""
         L = _lib.load()
         _dev(A.rowptr, A.colind)
         xt = _lib.SPX_F64 if xdtype == torch.float64 else _lib.SPX_F32
